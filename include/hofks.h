@@ -111,9 +111,11 @@ hofks_status hofks_set_state_f(hofks_ctx *ctx, const double *f, size_t bytes);
 
 /* Advance n_steps >= 0 time steps; asynchronous on the context's stream: it
  * returns once the last step is queued.  In a call of more than 16 steps on
- * a 2D or 3D grid it reads back the Euler sub-step count of earlier steps
- * (waiting for a step once it is 16 behind the one being queued), so that the
- * launches of the later steps follow a count that grows during the call. */
+ * a 2D or 3D grid (outside stream capture) it follows the Euler sub-step
+ * counts that the steps leave in pinned host memory, waiting for a step once
+ * it is two behind the one being queued, so that the launches of the later
+ * steps follow a count that grows during the call.
+ */
 hofks_status hofks_step(hofks_ctx *ctx, int n_steps);
 
 /* Wait for the stream and report the sticky device flag. */
@@ -152,8 +154,8 @@ hofks_status hofks_read_tail_substeps(hofks_ctx *ctx, long *n);
  * single-sub-step kernels followed by a persistent kernel that runs any
  * further sub-steps with an in-kernel barrier between them.  k = 0 (the
  * default) takes k = (sub-steps of the last step seen at a synchronising
- * call, or read back during a long hofks_step call) + 1, dropping the + 1
- * while that count is steady, and k = 1 on a 1D grid (scheme other than 3)
+ * call) + 1, or during a long hofks_step call the count of a step two behind
+ * extended by its trend, and k = 1 on a 1D grid (scheme other than 3)
  * that fits one persistent block, where the barrier is the block's own;
  * k >= 1 fixes it, so that k = 1 runs every sub-step after the first in the
  * persistent kernel.  The two kernels form the same faces from the same values; their

@@ -8,6 +8,7 @@
 // side by side on two streams; the update launch then forms U^{n+1} and the
 // next records cell by cell.
 #pragma once
+#include "dpp.hpp"
 #include "kernels.hpp"
 #include "slope.hpp"
 
@@ -84,43 +85,6 @@ __device__ __forceinline__ double block_max_1024(double v, double* red) {
   double m = red[0];
   for (int i = 1; i < (int)(blockDim.x >> 6); ++i) m = fmax(m, red[i]);
   return m;
-}
-
-// 1/x from the hardware reciprocal refined by two Newton steps (within a
-// few ulp of the IEEE quotient, and a shorter dependency chain)
-__device__ __forceinline__ double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return r;
-}
-
-// max(v, v of the lane that DPP control CTRL selects) for the rows in
-// ROW_MASK; lanes without a source keep v
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_max(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, ROW_MASK, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, ROW_MASK, 0xF,
-                                             false);
-  return fmax(v, __longlong_as_double(((long long)hi << 32) | (unsigned)lo));
-}
-
-// maximum over the wavefront, in every lane: row shifts by 1, 2, 4 and 8
-// leave each row's maximum in its lane 15, the row broadcasts carry rows 0
-// and 2 into rows 1 and 3 and then row 1 into rows 2 and 3, and lane 63 is
-// read back (cross-lane moves of the ALU instead of LDS permutes)
-__device__ __forceinline__ double wave_max_dpp(double v) {
-  v = dpp_max<0x111, 0xF>(v);
-  v = dpp_max<0x112, 0xF>(v);
-  v = dpp_max<0x114, 0xF>(v);
-  v = dpp_max<0x118, 0xF>(v);
-  v = dpp_max<0x142, 0xA>(v);
-  v = dpp_max<0x143, 0xC>(v);
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, 63);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // Flux F(U) of one 1D cell from U and 1/rho, with the expressions of

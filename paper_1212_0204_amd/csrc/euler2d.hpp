@@ -1,153 +1,188 @@
-// Euler sub-step on a 2D grid with LDS tiles (section 4.3.2, eq. (discmom)
-// with the limited slopes of the MUSCL flux).  One block advances a 16 x 16
-// tile of cells: it loads the tile and two halo cells on every side into
-// LDS, then for each axis in turn evaluates the split fluxes
-// W+- = F_a(U) +- alpha_a U once per cell (x: the 20 x 16 cells the x faces
-// need; y: the 16 x 20 cells the y faces need) into one buffer, every thread
-// adding the difference of its cell's two faces along that axis; then the
-// new value.  The per-cell form `euler_cell` evaluates ten fluxes and reads
-// 36 values from memory per cell; here it is 2.5 fluxes and about 1.6
-// values.  Same arithmetic per face; the speeds, the sub-step count and the
-// output buffers follow `k_euler_sub`.
+// Euler sub-steps on 2D grids (wavefront strips) and 3D grids (LDS tiles).
 #pragma once
+#include "dpp.hpp"
 #include "kernels.hpp"
+#include "slope.hpp"
 
 namespace hofks {
 
-constexpr int ET = 16;      // tile edge (cells)
-constexpr int EH = ET + 4;  // tile edge with two halo cells on each side
+// Euler sub-step on a 2D grid by wavefront strips (section 4.3.2, eq.
+// (discmom) with the limited slopes of the MUSCL flux).  A wavefront holds a
+// strip of 64 consecutive x cells, of which it advances the inner 60 on H
+// rows (y0 .. y0 + H - 1); lane l is cell X0 - 2 + l.
+//
+// The face flux psi_{j+1/2} = (W+_j + W-_{j+1})/2 + (s+_j - s-_{j+1})/4 is
+// taken as (R_j + L_{j+1})/2, R = W+ + s+/2 and L = W- - s-/2, so that a
+// cell needs two limited slopes per axis and moment instead of four.  Along
+// x the neighbours' values come by one-lane shifts of the ALU; along y the
+// wavefront marches over the rows y0 - 2 .. y0 + H + 1 and keeps the last
+// fluxes and half states in registers.  No LDS and no barrier except the
+// reduction of the speeds, so the blocks find room beside the kinetic
+// blocks.
+//
+// Bound by latency on small grids (launch, loads, the chain of a strip) and
+// by the FP64 issue rate from about 512^2 cells.  Measured per sub-step
+// against the form it replaced (16 x 16 LDS tiles, four slopes per face pair,
+// four block barriers): alone 9.2 -> 5.4 us on 70 x 37 cells, 8.8 -> 6.4 on
+// 256^2, 25.8 -> 12.3 on 512^2.
+constexpr int STRIP_W = 60;
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_euler_sub_tile(StepArgs<T> a, Geom G, int i, int ntx) {
+// The flux divergence of the H inner rows of a strip: row(q, U) gives the
+// moments of strip row q (0 .. H + 3, the lane's cell) and done(k, div) takes
+// twice the divergence (times dx) of inner row k as soon as it is complete.  Every
+// product and sum of a face is written out, so both cells of a face use the
+// same bits whichever wavefronts form it.
+template <int H, bool UNL, typename Row, typename Done>
+__device__ __forceinline__ void strip_div(const double* alpha, Row&& row, Done&& done) {
   constexpr int NM = 4;
+  double Wpp[NM] = {}, dP[NM] = {}, Wmp[NM] = {}, dM[NM] = {}, Rp[NM] = {}, Fp[NM] = {};  // last rows
+  double div[H][NM];
+#pragma unroll
+  for (int q = 0; q < H + 4; ++q) {
+    double U[NM];
+    row(q, U);
+    const double rho = U[0], ir = rcp3(rho);
+    const double u = U[1] * ir, v = U[2] * ir;
+    const double usq = fma(u, u, v * v);
+    const double p = 0.5 * fma(-rho, usq, 2.0 * U[3]);  // rho theta
+    const double Ep = U[3] + p;
+    if (q >= 2 && q < H + 2) {  // x faces of the row
+      const double F[NM] = {U[1], fma(U[1], u, p), U[2] * u, Ep * u};
+#pragma unroll
+      for (int r = 0; r < NM; ++r) {
+        const double wp = fma(alpha[0], U[r], F[r]), wm = fma(-alpha[0], U[r], F[r]);
+        const double dp = lane_next(wp) - wp, dm = lane_next(wm) - wm;
+        const double R = wp + half_slope<UNL>(lane_prev(dp), dp);
+        const double L = wm - half_slope<UNL>(lane_prev(dm), dm);
+        const double f = R + lane_next(L);
+        div[q - 2][r] = f - lane_prev(f);
+      }
+    }
+    const double F[NM] = {U[2], U[1] * v, fma(U[2], v, p), Ep * v};
+#pragma unroll
+    for (int r = 0; r < NM; ++r) {
+      const double wp = fma(alpha[1], U[r], F[r]), wm = fma(-alpha[1], U[r], F[r]);
+      double f = 0.0, R = 0.0;
+      const double dp = wp - Wpp[r], dm = wm - Wmp[r];
+      if (q >= 2 && q < H + 3) R = Wpp[r] + half_slope<UNL>(dP[r], dp);
+      if (q >= 3) {
+        const double L = Wmp[r] - half_slope<UNL>(dM[r], dm);
+        f = Rp[r] + L;  // face between rows q - 2 and q - 1
+        if (q >= 4) div[q - 4][r] += f - Fp[r];
+      }
+      Wpp[r] = wp;
+      Wmp[r] = wm;
+      dP[r] = dp;
+      dM[r] = dm;
+      Rp[r] = R;
+      Fp[r] = f;
+    }
+    if (q >= 4) done(q - 4, div[q - 4]);
+  }
+}
+
+// whether U is physical, and its speeds |u_a| + c (0 if not)
+__device__ __forceinline__ bool speeds2(const double* U, double gam, double* sp) {
+  const double ir = rcp3(U[0]);
+  const double u = U[1] * ir, v = U[2] * ir;
+  const double sq = fma(u, u, v * v);
+  const double p = 0.5 * fma(-U[0], sq, 2.0 * U[3]);
+  const bool ok = U[0] > 0.0 && p > 0.0 && isfinite(U[0]) && isfinite(p) && isfinite(sq);
+  const double c = ok ? sqrt(gam * p * ir) : 0.0;
+  sp[0] = ok ? fabs(u) + c : 0.0;
+  sp[1] = ok ? fabs(v) + c : 0.0;
+  return ok;
+}
+
+// map_axis for a strip's cells and rows, i >= -2: those past N + 1 are never
+// used and taken as N + 1, and an axis of two cells or more needs no division
+__device__ __forceinline__ int map_near(int i, int N, int bc) {
+  i = min(i, N + 1);
+  if (bc == 0 && N >= 2) return i < 0 ? i + N : (i >= N ? i - N : i);
+  return map_axis(i, N, bc);
+}
+
+template <typename T, int H, bool UNL>
+__global__ __launch_bounds__(256) void k_euler_strip(StepArgs<T> a, Geom G, int i, int nsx) {
+  constexpr int NM = 4, W = STRIP_W;
   double* S = a.set_r;
   const int Nx = G.n[0], Ny = G.n[1];
-  // contiguous ranges of tiles per die (blocks reach the dies round-robin),
-  // so that the halo of most tiles was written on the same die
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // contiguous ranges of blocks per die (blocks reach the dies round-robin)
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int X0 = (tile % ntx) * ET, Y0 = (tile / ntx) * ET;
-  const int t = threadIdx.x;
+  const int X0 = (tile % nsx) * W, y0 = ((tile / nsx) * 4 + wv) * H;
   const double* in = (i == 0) ? a.U_in : ((i & 1) ? a.UE1 : a.UE0);
   double* out = ((i + 1) & 1) ? a.UE1 : a.UE0;
 
-  __shared__ double Ut[NM][EH][EH];
-  // split fluxes along one axis at a time (x, then y) in one buffer:
-  // x: [+/-][r][y][x + 2] over 16 x 20 cells; y: [+/-][r][y + 2][x] over 20 x 16
-  __shared__ double Wb[2][NM][ET * EH];
-
-  // tile + halo (periodic wrap or outflow clamp, as the per-cell form),
-  // loaded before the speeds of the sub-step are read so that the two
-  // memory round trips overlap (both buffers exist whatever s is)
-  constexpr int NQ = (EH * EH + 255) / 256;
-  double Uload[NQ][NM];
+  // every row of the strip, loaded before the speeds of the sub-step are
+  // read so that the memory round trips overlap
+  const int gx = map_near(X0 - 2 + lane, Nx, G.bc[0]);
+  double Ur[H + 4][NM];
 #pragma unroll
-  for (int k = 0; k < NQ; ++k) {
-    const int q = t + k * 256;
-    if (q < EH * EH) {
-      const int hx = q % EH, hy = q / EH;
-      const int gx = map_axis(X0 + hx - 2, Nx, G.bc[0]);
-      const int gy = map_axis(Y0 + hy - 2, Ny, G.bc[1]);
-      const size_t j = (size_t)gy * Nx + gx;
+  for (int q = 0; q < H + 4; ++q) {
+    const size_t j = (size_t)map_near(y0 - 2 + q, Ny, G.bc[1]) * Nx + gx;
 #pragma unroll
-      for (int r = 0; r < NM; ++r) Uload[k][r] = in[(size_t)r * G.nc + j];
-    }
+    for (int r = 0; r < NM; ++r) Ur[q][r] = in[(size_t)r * G.nc + j];
   }
-  bool over;
-  const int s = substeps<2>(S, G, a.s_cap, &over);
-  if (i == 0) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
-      a.set_z[q] = 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      if (over) atomicOr(a.flag, FLAG_SUBSTEP);
-      a.flag[1] = s;
-    }
-  }
+  // speeds of the sub-step: lane 4 q + d reads axis d of slot q (row 0 has
+  // one slot)
+  const double* sp_row = S + (i == 0 ? 0 : ASTR + (size_t)(i - 1) * NSLOT * ASTR);
+  double al = sp_row[i == 0 ? lane & 1 : (lane & 31)];
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 ? open_substeps<2>(a, G) : a.flag[1];
   if (i >= s) return;
-  double alpha[3];
-  row_speeds<2>(S, i, alpha);
-  const double dts_dx = (G.dt / s) / G.dx;
-#pragma unroll
-  for (int k = 0; k < NQ; ++k) {
-    const int q = t + k * 256;
-    if (q < EH * EH) {
-#pragma unroll
-      for (int r = 0; r < NM; ++r) Ut[r][q / EH][q % EH] = Uload[k][r];
-    }
+  double alpha[2];
+  if (i == 0) {
+    alpha[0] = lane_value(al, 0);
+    alpha[1] = lane_value(al, 1);
+  } else {
+    al = dpp_max<0x114, 0xF>(al);                // lanes 4..: max with lane - 4
+    al = dpp_max<0x118, 0xF>(al);                // lanes 12..15: the row's four slots
+    alpha[0] = fmax(lane_value(al, 12), lane_value(al, 28));
+    alpha[1] = fmax(lane_value(al, 13), lane_value(al, 29));
   }
-  __syncthreads();
+  const double hdts_dx = 0.5 * ((G.dt / s) / G.dx);
+
   bool phys = true;
-  const int lx = t % ET, ly = t / ET;
-  const int gx = X0 + lx, gy = Y0 + ly;
-  const bool own = gx < Nx && gy < Ny;
-  double div[NM] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int ax = 0; ax < 2; ++ax) {
-    if (ax == 1) __syncthreads();  // the x faces have been read
-    // fluxes along ax: x for cells (x = -2..17, y = 0..15), y for (x = 0..15, y = -2..17)
-    for (int q = t; q < ET * EH; q += blockDim.x) {
-      const int hx = ax == 0 ? q % EH : q % ET + 2;
-      const int hy = ax == 0 ? q / EH + 2 : q / ET;
-      double Uq[NM];
-#pragma unroll
-      for (int r = 0; r < NM; ++r) Uq[r] = Ut[r][hy][hx];
-      double Wp[NM], Wm[NM];
-      phys &= split_flux<2>(Uq, ax, alpha[ax], G.gam, Wp, Wm);
-#pragma unroll
-      for (int r = 0; r < NM; ++r) {
-        Wb[0][r][q] = Wp[r];
-        Wb[1][r][q] = Wm[r];
-      }
-    }
-    __syncthreads();
-    if (own) {
-#pragma unroll
-      for (int r = 0; r < NM; ++r) {
-        // cells l-2 .. l+2 along ax: x -> entries ly*EH + lx + k, y -> (ly + k)*ET + lx
-        double wp[5], wm[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const int e = ax == 0 ? ly * EH + lx + k : (ly + k) * ET + lx;
-          wp[k] = Wb[0][r][e];
-          wm[k] = Wb[1][r][e];
-        }
-        const double spl = vl_slope(wp[1] - wp[0], wp[2] - wp[1], a.unlimited);
-        const double sml = vl_slope(wm[2] - wm[1], wm[3] - wm[2], a.unlimited);
-        const double spr = vl_slope(wp[2] - wp[1], wp[3] - wp[2], a.unlimited);
-        const double smr = vl_slope(wm[3] - wm[2], wm[4] - wm[3], a.unlimited);
-        const double psil = 0.5 * (wp[1] + wm[2]) + 0.25 * (spl - sml);
-        const double psir = 0.5 * (wp[2] + wm[3]) + 0.25 * (spr - smr);
-        div[r] += psir - psil;
-      }
-    }
-  }
   double mx[2] = {0.0, 0.0};
-  if (own) {
-    double Un[NM];
+  const bool ownx = lane >= 2 && lane < 2 + W && X0 + lane - 2 < Nx;
+  strip_div<H, UNL>(
+      alpha,
+      [&](int q, double* U) {
 #pragma unroll
-    for (int r = 0; r < NM; ++r) Un[r] = Ut[r][ly + 2][lx + 2] - dts_dx * div[r];
-    const size_t j = (size_t)gy * Nx + gx;
+        for (int r = 0; r < NM; ++r) U[r] = Ur[q][r];
+      },
+      [&](int k, const double* div) {
+        const int y = y0 + k;
+        const double* Uc = Ur[k + 2];
+        double Un[NM], sp[2];
 #pragma unroll
-    for (int r = 0; r < NM; ++r) out[(size_t)r * G.nc + j] = Un[r];
-    if (i + 1 < s) {
-      double sp[3];
-      phys &= lf_speeds<2>(Un, G.gam, sp);
-      mx[0] = sp[0];
-      mx[1] = sp[1];
-    }
-  }
+        for (int r = 0; r < NM; ++r) Un[r] = fma(-hdts_dx, div[r], Uc[r]);
+        if (!ownx || y >= Ny) return;
+        phys &= i > 0 || speeds2(Uc, G.gam, sp);  // U^n; later inputs were checked as results
+        const size_t j = (size_t)y * Nx + X0 + lane - 2;
+#pragma unroll
+        for (int r = 0; r < NM; ++r) out[(size_t)r * G.nc + j] = Un[r];
+        if (i + 1 < s) {
+          phys &= speeds2(Un, G.gam, sp);
+          mx[0] = fmax(mx[0], sp[0]);
+          mx[1] = fmax(mx[1], sp[1]);
+        }
+      });
   if (!phys) atomicOr(a.flag, FLAG_NONPHYS);
   if (i + 1 < s) {
-    __shared__ double wm4[4][ASTR];
+    __shared__ double wm4[2][4];
 #pragma unroll
     for (int d2 = 0; d2 < 2; ++d2) {
-      const double m = wave_max(mx[d2]);
-      if ((t & 63) == 0) wm4[t >> 6][d2] = m;
+      const double m = wave_max_dpp(mx[d2]);
+      if (lane == 0) wm4[d2][wv] = m;
     }
     __syncthreads();
-    if (t < 2) {
-      double m = wm4[0][t];
-      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmax(m, wm4[w][t]);
-      atomic_max_pos(speed_row(S, i + 1, blockIdx.x % NSLOT) + t, m);
+    if (threadIdx.x < 2) {
+      const double* m = wm4[threadIdx.x];
+      atomic_max_pos(speed_row(S, i + 1, blockIdx.x % NSLOT) + threadIdx.x,
+                     fmax(fmax(m[0], m[1]), fmax(m[2], m[3])));
     }
   }
 }
@@ -179,16 +214,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(64))) void k_eu
   __shared__ double Ub[NM][B3Z * B3Y * B3X];  // box: [z][y][x]
   __shared__ double Wb[2][NM][256];          // split fluxes along one axis
 
-  bool over;
-  const int s = substeps<3>(S, G, a.s_cap, &over);
-  if (i == 0) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
-      a.set_z[q] = 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      if (over) atomicOr(a.flag, FLAG_SUBSTEP);
-      a.flag[1] = s;
-    }
-  }
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 ? open_substeps<3>(a, G) : a.flag[1];
   if (i >= s) return;
   double alpha[3];
   row_speeds<3>(S, i, alpha);

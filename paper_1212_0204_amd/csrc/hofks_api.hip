@@ -285,8 +285,8 @@ struct hofks_ctx {
   double tau;
   int s_cap;
   int s_known;  // Euler sub-steps of the last step seen by the host
-  int s_margin;  // spare single-sub-step launches beyond s_known (0 or 1)
-  int euler_k;  // > 0: per-sub-step Euler launches before the tail (0: s_known + 1)
+  int s_next;   // single-sub-step Euler launches of the step being queued
+  int euler_k;  // > 0: per-sub-step Euler launches before the tail (0: s_next)
   bool euler_seq;   // the Euler solve runs on the caller's stream before the kinetic kernel
   bool strang;      // Strang splitting: half relaxations around each transport
   double inv_prev;  // 1/tau of the last step taken (Strang)
@@ -312,16 +312,11 @@ struct hofks_ctx {
   // caller's stream with two events, beside the kinetic kernel
   hipStream_t aux;
   hipEvent_t ev_fork, ev_join;
-  // the Euler sub-step count of a recent step, read back during long step
-  // calls: the auxiliary stream copies it to pinned host memory after the
-  // step's Euler launches and marks the copy (ev_peek)
-  hipEvent_t ev_peek;
-  int* peek_h;
-  bool peek_now;      // copy the count of the step being queued
-  bool peek_pending;
-  long peek_at;     // step after which the pending read was queued
-  long peek_next;   // first step at which the next read may be queued
-  int peek_every;   // steps between reads: 8 while the count moves, doubling to 64 while not
+  // pinned host ring written by sub-step 0 of every 2D/3D step (see
+  // StepArgs::s_host); ticks number the steps queued on this context, the
+  // one after tick0 being the first since the state or tau was set
+  unsigned long long *s_ring, *s_ring_dev;
+  unsigned tick, tick0;
   // closure form (2D-2V): network (caller's device memory), scale of its
   // output, indicator threshold; per-cell arrays in the workspace
   const void* clos_w;
@@ -572,23 +567,6 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st);
 
 // Euler launches of the step on the auxiliary stream, after everything
 // already queued on the caller's stream
-// the step's sub-step count to the host on the auxiliary stream, after its
-// Euler launches there (or, with the Euler solve on the caller's stream, after
-// an event that follows them), beside the update
-hofks_status queue_peek(hofks_ctx* c) {
-  c->peek_now = false;
-  if (c->euler_seq) {  // the auxiliary stream is idle in this form
-    HIPCHK(c, hipEventRecord(c->ev_fork, c->stream));
-    HIPCHK(c, hipStreamWaitEvent(c->aux, c->ev_fork, 0));
-  }
-  HIPCHK(c, hipMemcpyAsync(c->peek_h, c->flag + 1, sizeof(int), hipMemcpyDeviceToHost, c->aux));
-  HIPCHK(c, hipEventRecord(c->ev_peek, c->aux));
-  c->peek_pending = true;
-  c->peek_at = c->steps;
-  c->peek_next = c->steps + c->peek_every;
-  return HOFKS_OK;
-}
-
 template <int D, typename T>
 hofks_status fork_euler(hofks_ctx* c, const StepArgs<T>& a) {
   if (c->euler_seq) {  // before the kinetic kernel, on the caller's stream
@@ -597,7 +575,7 @@ hofks_status fork_euler(hofks_ctx* c, const StepArgs<T>& a) {
       launch_euler<D, T>(c, a, c->stream);
       HIPCHK(c, hipGetLastError());
     }
-    return c->peek_now ? queue_peek(c) : HOFKS_OK;
+    return HOFKS_OK;
   }
   // within one hofks_step call the previous step recorded the fork point
   // right after U^{n+1} was formed, before its records
@@ -612,7 +590,7 @@ hofks_status fork_euler(hofks_ctx* c, const StepArgs<T>& a) {
     HIPCHK(c, hipGetLastError());
   }
   HIPCHK(c, hipEventRecord(c->ev_join, c->aux));
-  return c->peek_now ? queue_peek(c) : HOFKS_OK;
+  return HOFKS_OK;
 }
 
 // join the Euler launches and run the per-cell update on the caller's stream
@@ -640,14 +618,29 @@ hofks_status join_update(hofks_ctx* c, const StepArgs<T>& a) {
   return HOFKS_OK;
 }
 
+// Rows per strip of the 2D Euler sub-steps.  Short grids want many strips:
+// with one row a sub-step alone takes 5.4 us on 70 x 37 cells and 6.4 on
+// 256^2 (two rows: 6.5 and 6.3, and beside the kinetic kernel 17.5 -> 21.1 on
+// 256^2, where the longer chain of a wavefront shows), up to two blocks per
+// compute unit.  Larger grids are bound by the FP64 issue rate, where more
+// rows share more of the y fluxes and slopes, and by the last round of
+// blocks, so the fewest rows that give each compute unit at most one block:
+// 512^2 alone 15.5 us with one row, 12.8 with three, 14.4 with four (288
+// blocks) and 12.3 with five (234 blocks).
+int strip_rows(const Plan& P) {
+  const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
+  auto blocks = [&](int H) { return nsx * ((P.G.n[1] + 4 * H - 1) / (4 * H)); };
+  if (blocks(1) <= 2 * P.ncu) return 1;
+  if (blocks(2) <= P.ncu) return 2;
+  return blocks(3) <= P.ncu ? 3 : 5;
+}
+
 // Euler solve of a step: one launch per sub-step for the first K = (last
-// known count + margin) sub-steps (the kernel boundary is the grid-wide
-// barrier), then a persistent tail that runs any further sub-steps with an
-// in-kernel barrier (it returns at once when K >= s).  The spare launch (margin
-// 1) absorbs a count that grows by one; each launch with i >= s still costs a
-// kernel boundary on the solve's critical path, so it is dropped while the
-// read-back sees a steady count, and a single sub-step left to the tail is
-// about as cheap.
+// known count + a margin, see plan_launches) sub-steps (the kernel boundary is
+// the grid-wide barrier), then a persistent tail that runs any further
+// sub-steps with an in-kernel barrier (it returns at once when K >= s).  Each
+// launch with i >= s still costs a kernel boundary on the solve's critical
+// path.
 template <int D, typename T>
 void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
   const Plan& P = c->P;
@@ -657,7 +650,7 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
   const int K = std::max(
       1, std::min(c->s_cap, c->euler_k > 0 ? c->euler_k
                             : one_block    ? 1
-                                           : c->s_known + c->s_margin));
+                                           : c->s_next));
   if (c->desc.scheme == 3) {  // WENO: three Runge-Kutta stage launches per sub-step
     if constexpr (D == 2) {  // 16 x 16 LDS tiles
       const int ntx = (P.G.n[0] + WT - 1) / WT, nty = (P.G.n[1] + WT - 1) / WT;
@@ -674,10 +667,19 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     hipLaunchKernelGGL((k_weno_tail<D, T, 256>), dim3(P.GE), dim3(256), 0, st, a, P.G, K);
     return;
   }
-  if constexpr (D == 2) {  // 16 x 16 LDS tiles
-    const int ntx = (P.G.n[0] + ET - 1) / ET, nty = (P.G.n[1] + ET - 1) / ET;
-    for (int i = 0; i < K; ++i)
-      hipLaunchKernelGGL((k_euler_sub_tile<T>), dim3(ntx * nty), dim3(256), 0, st, a, P.G, i, ntx);
+  if constexpr (D == 2) {  // wavefront strips of 60 x H cells
+    const int H = strip_rows(P);
+    const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
+    const unsigned nb = (unsigned)(nsx * ((P.G.n[1] + 4 * H - 1) / (4 * H)));
+#define KE(HH, U)                                                                              \
+  hipLaunchKernelGGL((k_euler_strip<T, HH, U>), dim3(nb), dim3(256), 0, st, a, P.G, i, nsx)
+#define KH(HH) \
+  if (a.unlimited) KE(HH, true); else KE(HH, false);
+    for (int i = 0; i < K; ++i) {
+      if (H == 1) { KH(1) } else if (H == 2) { KH(2) } else if (H == 3) { KH(3) } else { KH(5) }
+    }
+#undef KH
+#undef KE
   } else if constexpr (D == 3) {  // 8 x 4 x 4 LDS tiles
     const int ntx = (P.G.n[0] + E3X - 1) / E3X, nty = (P.G.n[1] + E3Y - 1) / E3Y;
     const int ntz = (P.G.n[2] + E3Z - 1) / E3Z;
@@ -731,6 +733,8 @@ hofks_status launch_step(hofks_ctx* c, float* snap_x = nullptr, float* snap_t = 
   a.thr = 0.0;
   a.sums = (double*)(c->ws + P.off_sums);
   a.nstep = n;
+  a.s_host = D >= 2 ? c->s_ring_dev : nullptr;
+  a.tick = ++c->tick;
   const bool ft = (P.G.mu == 0.0);
   const bool eul = !ft && c->desc.scheme != 1;
   if (c->clos_dirty && !eul) {
@@ -847,57 +851,77 @@ hofks_status launch_closure_step(hofks_ctx* c, StepArgs<T>& a, float* snap_x, fl
   return HOFKS_OK;
 }
 
-// Within a long step call on a 2D or 3D grid the host reads back the Euler
-// sub-step count of a step some steps behind the one it queues, so that the
-// per-sub-step Euler launches of the later steps follow a count that grows
-// during the call (otherwise the persistent tail, slower per sub-step beside
-// the kinetic kernel, runs the growth).  Reads are 8 steps apart while the
-// count moves and up to 64 while it does not; while two reads agree the spare
-// Euler launch is dropped.  The host waits for the step a
-// read follows only when it is PEEK_LAG steps ahead of it, so the device
-// keeps that many steps queued; the wait polls (a blocking wait wakes up
-// late).  On 1D grids the tail is the faster form.
-constexpr long PEEK_LAG = 16;
-constexpr int PEEK_MIN = 8, PEEK_MAX = 64;
+// Launches of the next step's Euler solve.  Without newer counts the last
+// one known plus a spare.  Within a long step call on a 2D or 3D grid the host
+// follows c dt sum alpha / dx of the step PEEK_LAG steps behind the one it
+// queues, which that step's sub-step 0 leaves in pinned host memory, and
+// extends its trend over the steps in between: a sub-step left to the
+// persistent tail costs several launches (on the 512^2 disk, whose count goes
+// 8 -> 18 in 20 steps, a third of all sub-steps ran there when counts were read
+// back 16 steps behind).  The wait keeps at most PEEK_LAG steps queued,
+// more than the host takes to queue one; it polls memory and looks at the
+// stream now and then, so that it ends if the device fails.  On 1D grids
+// the tail is the faster form.
+constexpr int LONG_CALL = 16, PEEK_LAG = 2;
 
-hofks_status peek_substeps(hofks_ctx* c) {
-  if (c->peek_pending) {
-    hipError_t q = hipEventQuery(c->ev_peek);
-    if (q == hipErrorNotReady) {
-      (void)hipGetLastError();  // clear the status the query leaves
-      if (c->steps - c->peek_at < PEEK_LAG) return HOFKS_OK;
-      do {
-        q = hipEventQuery(c->ev_peek);
-        if (q == hipErrorNotReady) (void)hipGetLastError();
-      } while (q == hipErrorNotReady);
-    }
-    if (q != hipSuccess) return fmt_err(c->err, "step count read-back failed"), HOFKS_EDEVICE;
-    const int sv = *c->peek_h;
-    c->peek_every = (sv > 0 && sv != c->s_known) ? PEEK_MIN : std::min(PEEK_MAX, 2 * c->peek_every);
-    if (sv > 0) c->s_known = sv;
-    c->peek_pending = false;
-  }
-  return HOFKS_OK;
+double ring_value(const hofks_ctx* c, unsigned t) {  // < 0: not written
+  const unsigned long long w = __atomic_load_n(c->s_ring + t % S_RING, __ATOMIC_RELAXED);
+  if ((unsigned)(w >> 32) != t) return -1.0;
+  const unsigned b = (unsigned)w;
+  float f;
+  std::memcpy(&f, &b, sizeof(f));
+  return f >= 0.0f ? (double)f : 0.0;  // (also no NaN)
 }
 
-// whether the step about to be queued copies its sub-step count back
-bool peek_due(const hofks_ctx* c) {
-  // (a step count set back by a new state leaves peek_next far ahead: read)
-  return !c->peek_pending && (c->steps >= c->peek_next || c->peek_next - c->steps > PEEK_MAX);
+hofks_status plan_launches(hofks_ctx* c, bool follow) {
+  c->s_next = c->s_known + 1;
+  const unsigned t = c->tick + 1 - PEEK_LAG;  // the step followed
+  if (!follow) return HOFKS_OK;
+  if ((int)(t - c->tick0) <= 0) {  // first steps from a state: its count may jump
+    c->s_next += 3;
+    return HOFKS_OK;
+  }
+  double v = ring_value(c, t);
+  for (unsigned it = 1; v < 0.0; v = ring_value(c, t), ++it) {
+    if (it % 4096 == 0) {
+      const hipError_t q = hipStreamQuery(c->stream);
+      if (q == hipErrorNotReady) {
+        (void)hipGetLastError();  // clear the status the query leaves
+        continue;
+      }
+      if (q != hipSuccess) return hip_fail(c, q, "waiting for a step");
+      v = ring_value(c, t);
+      if (v < 0.0) return HOFKS_OK;  // overwritten by a replay of captured steps
+      break;
+    }
+  }
+  // growth over the PEEK_LAG steps before t, or twice that of the one before
+  const bool two = (int)(t - PEEK_LAG - c->tick0) > 0;
+  const double old = two ? ring_value(c, t - PEEK_LAG)
+                         : (int)(t - 1 - c->tick0) > 0 ? ring_value(c, t - 1) : v - 1.5;
+  double grown = old >= 0.0 && v > old ? (two ? 1.25 : 2.0) * (v - old) : 0.0;
+  grown = std::min(grown, 6.0);
+  c->s_known = std::max(1, std::min(c->s_cap, (int)std::ceil(v)));
+  c->s_next = std::max(1, (int)std::ceil(std::min(v + grown + 0.02, (double)SMAX)));
+  return HOFKS_OK;
 }
 
 template <int D, typename T>
 hofks_status step_impl(hofks_ctx* c, int nsteps) {
   c->fork_pending = false;
   hofks_status st = HOFKS_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool eul = c->P.G.mu != 0.0 && c->desc.scheme != 1;
+  bool follow = D >= 2 && eul && c->euler_k == 0 && nsteps > LONG_CALL;
+  if (follow) {  // captured steps do not run while the host waits
+    HIPCHK(c, hipStreamIsCapturing(c->stream, &cap));
+    follow = cap == hipStreamCaptureStatusNone;
+  }
   for (int it = 0; it < nsteps && !st; ++it) {
     c->fork_next = it + 1 < nsteps;
     if (c->strang) set_step_weights(c);
-    const bool peek = c->euler_k == 0 && D >= 2 && nsteps > PEEK_LAG;
-    if (peek) st = peek_substeps(c);
+    st = plan_launches(c, follow);
     if (st) break;
-    c->peek_now = peek && peek_due(c);
-    c->s_margin = peek && c->peek_every > PEEK_MIN ? 0 : 1;  // two reads agreed
     st = launch_step<D, T>(c);
     if (st) break;
     c->cur ^= 1;
@@ -906,7 +930,6 @@ hofks_status step_impl(hofks_ctx* c, int nsteps) {
   }
   if (c->strang) set_step_weights(c);
   c->fork_next = c->fork_pending = false;
-  c->s_margin = 1;
   return st;
 }
 
@@ -935,22 +958,10 @@ hofks_status zero_ints(hofks_ctx* c, int* p, int n) {
   return HOFKS_OK;
 }
 
-// a sub-step count read back for an earlier step, still in flight, would
-// later replace a newer one: wait for it and drop it
-hofks_status drop_peek(hofks_ctx* c) {
-  if (c->peek_pending) {
-    HIPCHK(c, hipEventSynchronize(c->ev_peek));
-    c->peek_pending = false;
-  }
-  return HOFKS_OK;
-}
-
 hofks_status read_flag(hofks_ctx* c) {
   int h[2] = {0, 0};
   HIPCHK(c, hipMemcpyAsync(h, c->flag, sizeof(h), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  hofks_status st = drop_peek(c);
-  if (st) return st;
   if (h[1] > 0) c->s_known = h[1];
   if (h[0] & FLAG_SPIN) {
     fmt_err(c->err, "a bounded wait of the step kernel gave up; results are invalid");
@@ -977,11 +988,8 @@ hofks_status plan_substeps(hofks_ctx* c) {
   const double sv = std::ceil(c->P.G.sfac * c->P.G.dt * sum / c->P.G.dx);
   const int s0 = (sv >= 1.0 && sv < SMAX) ? (int)sv : (sv >= SMAX ? SMAX : 1);
   c->s_cap = std::min(SMAX, std::max(2 * s0, s0 + 8));
-  hofks_status st = drop_peek(c);  // the count of the previous state
-  if (st) return st;
   c->s_known = s0;
-  c->peek_every = PEEK_MIN;
-  c->peek_next = 0;
+  c->tick0 = c->tick;  // counts of earlier steps are of another state
   return HOFKS_OK;
 }
 
@@ -1092,20 +1100,19 @@ hofks_status hofks_create(const hofks_grid_desc* desc, void* dev_ws, size_t ws_b
   if (hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_fork, evf) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_join, evf) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_peek, hipEventDisableTiming) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->peek_h), sizeof(int), hipHostMallocDefault) !=
+      hipHostMalloc(reinterpret_cast<void**>(&c->s_ring), S_RING * sizeof(*c->s_ring),
+                    hipHostMallocMapped) != hipSuccess ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&c->s_ring_dev), c->s_ring, 0) !=
           hipSuccess) {
     hofks_destroy(c);
     return HOFKS_EDEVICE;
   }
-  *c->peek_h = 0;
-  c->peek_pending = false;
-  c->peek_every = PEEK_MIN;
-  c->peek_next = 0;
+  std::memset(c->s_ring, 0, S_RING * sizeof(*c->s_ring));
+  c->tick = c->tick0 = 0;
   c->tau = INFINITY;
   c->s_cap = 1;
   c->s_known = 1;
-  c->s_margin = 1;
+  c->s_next = 1;
   // kinetic configuration before any tuning: wider unroll in 2D/3D, two
   // wavefronts per block for the FP64 2D grid
   c->kng = (P.d == 2 && !P.prec) ? 2 : 4;
@@ -2635,9 +2642,11 @@ hofks_status hofks_mlp_adam(float* params, const float* grad, float* m, float* v
 extern "C" void hofks_destroy(hofks_ctx* c) {
   if (!c) return;
   batch_free(c);
-  if (c->aux) (void)hipStreamSynchronize(c->aux);  // a read-back may be in flight
-  if (c->ev_peek) (void)hipEventDestroy(c->ev_peek);
-  if (c->peek_h) (void)hipHostFree(c->peek_h);
+  if (c->s_ring) {  // steps in flight write it (on the caller's stream or aux)
+    (void)hipStreamSynchronize(c->stream);
+    if (c->aux) (void)hipStreamSynchronize(c->aux);
+    (void)hipHostFree(c->s_ring);
+  }
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);

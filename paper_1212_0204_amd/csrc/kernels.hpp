@@ -114,10 +114,12 @@ __device__ __forceinline__ unsigned load_acquire(unsigned* p) {
 // bound dt_s sum alpha <= dx/2 of eq. (Time2), 2.5 for the WENO solve's 0.4)
 template <int D>
 __device__ __forceinline__ int substeps(const double* alpha0, const Geom& G, int s_cap,
-                                        bool* over) {
+                                        bool* over, double* raw = nullptr) {
   double sum = 0.0;
   for (int a = 0; a < D; ++a) sum += alpha0[a];
-  double sv = ceil(G.sfac * G.dt * sum / G.dx);
+  double sv = G.sfac * G.dt * sum / G.dx;
+  if (raw) *raw = sv;
+  sv = ceil(sv);
   int s = (sv >= 1.0) ? (sv <= (double)s_cap ? (int)sv : s_cap + 1) : 1;
   *over = (s > s_cap);
   return s > s_cap ? s_cap : s;
@@ -524,7 +526,32 @@ struct StepArgs {
   double thr;
   double* sums;  // [2 (d+2)][nc]: moment sums of f* and of E, for k_cell_update
   long nstep;    // n of the step t^n -> t^{n+1} (off-lattice shifts)
+  // pinned host ring of S_RING words for the host's launch counts (or null):
+  // (tick << 32) | FP32 bits of c dt sum_a alpha_a / dx at this step
+  unsigned long long* s_host;
+  unsigned tick;
 };
+constexpr unsigned S_RING = 16;
+
+// sub-step 0 of a step: the count of the step, by one block, to the flag
+// words and to the host's ring; the set of the step after next cleared by all
+template <int D, typename T>
+__device__ __forceinline__ int open_substeps(const StepArgs<T>& a, const Geom& G) {
+  bool over;
+  double raw;
+  const int s = substeps<D>(a.set_r, G, a.s_cap, &over, &raw);
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
+    a.set_z[q] = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (over) atomicOr(a.flag, FLAG_SUBSTEP);
+    a.flag[1] = s;
+    if (a.s_host)
+      __hip_atomic_store(a.s_host + a.tick % S_RING,
+                         ((unsigned long long)a.tick << 32) | __float_as_uint((float)raw),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  return s;
+}
 
 // Euler sub-step i (eq. (discmom) with the flux of section 4.3), one cell per
 // thread over the whole grid: sub-step 0 also clears the set of the step
@@ -536,16 +563,8 @@ template <int D, typename T>
 __global__ __launch_bounds__(256) void k_euler_sub(StepArgs<T> a, Geom G, int i) {
   constexpr int NM = D + 2;
   double* S = a.set_r;
-  bool over;
-  const int s = substeps<D>(S, G, a.s_cap, &over);
-  if (i == 0) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
-      a.set_z[q] = 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      if (over) atomicOr(a.flag, FLAG_SUBSTEP);
-      a.flag[1] = s;
-    }
-  }
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 ? open_substeps<D>(a, G) : a.flag[1];
   if (i >= s) return;
   double alpha[3];
   row_speeds<D>(S, i, alpha);

@@ -124,16 +124,8 @@ template <int D, typename T>
 __global__ __launch_bounds__(256) void k_weno_stage(StepArgs<T> a, Geom G, int i, int st) {
   constexpr int NM = D + 2;
   double* S = a.set_r;
-  bool over;
-  const int s = substeps<D>(S, G, a.s_cap, &over);
-  if (i == 0 && st == 0) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
-      a.set_z[q] = 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      if (over) atomicOr(a.flag, FLAG_SUBSTEP);
-      a.flag[1] = s;
-    }
-  }
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 && st == 0 ? open_substeps<D>(a, G) : a.flag[1];
   if (i >= s) return;
   double alpha[3];
   row_speeds<D>(S, i, alpha);
@@ -328,16 +320,8 @@ __global__ __launch_bounds__(256) void k_weno_stage_tile(StepArgs<T> a, Geom G, 
   __shared__ double Hs[2][NM][WH * WT];     // split fluxes along one axis
   __shared__ double Fc[NM][WF * WT];        // face values along one axis
 
-  bool over;
-  const int s = substeps<2>(S, G, a.s_cap, &over);
-  if (i == 0 && st == 0) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < SET_D; q += gridDim.x * blockDim.x)
-      a.set_z[q] = 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      if (over) atomicOr(a.flag, FLAG_SUBSTEP);
-      a.flag[1] = s;
-    }
-  }
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 && st == 0 ? open_substeps<2>(a, G) : a.flag[1];
   if (i >= s) return;
   double alpha[3];
   row_speeds<2>(S, i, alpha);

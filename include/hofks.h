@@ -155,8 +155,9 @@ hofks_status hofks_read_tail_substeps(hofks_ctx *ctx, long *n);
  * further sub-steps with an in-kernel barrier between them.  k = 0 (the
  * default) takes k = (sub-steps of the last step seen at a synchronising
  * call) + 1, or during a long hofks_step call the count of a step two behind
- * extended by its trend, and k = 1 on a 1D grid (scheme other than 3)
- * that fits one persistent block, where the barrier is the block's own;
+ * extended by its trend; a 1D grid of at most 4032 cells (scheme other than
+ * 3; in the precision form where lambda < 1e-5) then runs every sub-step in
+ * one launch of one block, without a tail.
  * k >= 1 fixes it, so that k = 1 runs every sub-step after the first in the
  * persistent kernel.  The two kernels form the same faces from the same values; their
  * results agree to rounding (the compiler may contract their products

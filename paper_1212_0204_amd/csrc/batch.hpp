@@ -8,9 +8,8 @@
 // side by side on two streams; the update launch then forms U^{n+1} and the
 // next records cell by cell.
 #pragma once
-#include "dpp.hpp"
+#include "euler1d.hpp"
 #include "kernels.hpp"
-#include "slope.hpp"
 
 namespace hofks {
 
@@ -87,52 +86,6 @@ __device__ __forceinline__ double block_max_1024(double v, double* red) {
   return m;
 }
 
-// Flux F(U) of one 1D cell from U and 1/rho, with the expressions of
-// split_flux (W+- = F +- alpha U); false if the state is not physical
-__device__ __forceinline__ bool flux1(const double* U, double irho, double* F) {
-  const double rho = U[0];
-  const double u = U[1] * irho;
-  const double usq = u * u;
-  const double p = fma(-rho, usq, 2.0 * U[2]);
-  F[0] = U[1];
-  F[1] = fma(U[1], u, p);
-  F[2] = (U[2] + p) * u;
-  return (rho > 0.0) && (p > 0.0) && isfinite(rho) && isfinite(p) && isfinite(usq);
-}
-
-// Lax-Friedrichs speed |u| + sqrt(gam p / rho) of one 1D cell (p = rho
-// theta) from U and 1/rho; 0 and false if the state is not physical
-__device__ __forceinline__ bool speed1(const double* U, double irho, double gam, double* sp) {
-  const double rho = U[0];
-  const double u = U[1] * irho;
-  const double usq = u * u;
-  const double p = fma(-rho, usq, 2.0 * U[2]);
-  const bool ok = (rho > 0.0) && (p > 0.0) && isfinite(rho) && isfinite(p) && isfinite(usq);
-  *sp = ok ? fabs(u) + sqrt(gam * p * irho) : 0.0;
-  return ok;
-}
-
-// W+ (w[0..2]) and W- (w[3..5]) of one cell
-__device__ __forceinline__ void wsplit(const double* U, const double* F, double alpha, double* w) {
-#pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    w[r] = fma(alpha, U[r], F[r]);
-    w[3 + r] = fma(-alpha, U[r], F[r]);
-  }
-}
-
-// face flux between the cells of entries 1 and 2 of a four-entry window
-// (the face arithmetic of section 4.3.2 as in the other Euler forms)
-__device__ __forceinline__ void face4(const double* w0, const double* w1, const double* w2,
-                                      const double* w3, double* fc) {
-#pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    const double spl = vl_slope_sel(w1[r] - w0[r], w2[r] - w1[r]);
-    const double sml = vl_slope_sel(w2[3 + r] - w1[3 + r], w3[3 + r] - w2[3 + r]);
-    fc[r] = fma(0.25, spl - sml, 0.5 * (w1[r] + w2[3 + r]));
-  }
-}
-
 // Euler solve of one tube by segments of EUL_TPB cells (eq. (discmom) with
 // the limited slopes of section 4.3.2): per sub-step and segment the block
 // evaluates the split fluxes W+- of the segment and two cells on each side
@@ -168,7 +121,7 @@ __device__ void batch_euler_seg(const BatchArgs& a, int t, double* L, double* re
   const double* U0 = a.dar + (p ? T.U[1] : T.U[0]);
   double* UE0 = a.dar + T.UE[0];
   double* UE1 = a.dar + T.UE[1];
-  const double dts_dx = (G.dt / s) / G.dx;
+  const double hdts = 0.5 * ((G.dt / s) / G.dx);
   bool phys = true;
   for (int i = 0; i < s; ++i) {
     const double* in = (i == 0) ? U0 : ((i & 1) ? UE1 : UE0);
@@ -197,9 +150,9 @@ __device__ void batch_euler_seg(const BatchArgs& a, int t, double* L, double* re
         const double* w = Wl + f * 6;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
-          const double spl = vl_slope_sel(w[6 + r] - w[r], w[12 + r] - w[6 + r]);
-          const double sml = vl_slope_sel(w[15 + r] - w[9 + r], w[21 + r] - w[15 + r]);
-          Pl[f * 3 + r] = fma(0.25, spl - sml, 0.5 * (w[6 + r] + w[15 + r]));
+          const double hp = half_slope<false>(w[6 + r] - w[r], w[12 + r] - w[6 + r]);
+          const double hm = half_slope<false>(w[15 + r] - w[9 + r], w[21 + r] - w[15 + r]);
+          Pl[f * 3 + r] = face2(w[6 + r], hp, w[15 + r], hm);
         }
       }
       __syncthreads();
@@ -209,7 +162,7 @@ __device__ void batch_euler_seg(const BatchArgs& a, int t, double* L, double* re
         double Un[3];
 #pragma unroll
         for (int r = 0; r < 3; ++r)
-          Un[r] = fma(-dts_dx, Pl[(c + 1) * 3 + r] - Pl[c * 3 + r], in[(size_t)r * Nx + j]);
+          Un[r] = fma(-hdts, Pl[(c + 1) * 3 + r] - Pl[c * 3 + r], in[(size_t)r * Nx + j]);
 #pragma unroll
         for (int r = 0; r < 3; ++r) out[(size_t)r * Nx + j] = Un[r];
         if (i + 1 < s) {
@@ -225,46 +178,20 @@ __device__ void batch_euler_seg(const BatchArgs& a, int t, double* L, double* re
   if (!phys) atomicOr(a.tflag + t, FLAG_NONPHYS);
 }
 
-// Euler solve of one tube of at most NT * CPT cells with every cell's
-// moments (and 1/rho) in registers for all s sub-steps, by NT threads of
-// the block: thread t of the group owns the CPT consecutive cells
-// t CPT .. t CPT + CPT - 1, so a face stencil reaches at most two cells into
-// each neighbouring thread.  After every sub-step a thread leaves U and 1/rho
-// of its first two and last two cells in its LDS slots, which the
-// neighbouring lanes of its wavefront read during the next sub-step (a
-// wavefront's LDS operations complete in order, so lanes of one wavefront
-// need no barrier); at the ends of a wavefront the cells come from the edge
-// set that each wavefront leaves for its neighbours (one set per sub-step
-// parity, so one block barrier per sub-step suffices, which also publishes
-// the wavefront speed maxima that make alpha).  A thread forms the split
-// fluxes of each stencil entry as it enters a four-entry window, the left
-// faces of its cells and the right face of its last cell (which its right
-// neighbour forms too, from the same values with the same arithmetic), and
-// updates its cells.  Outflow ends: entries before cell 0 repeat cell 0,
-// those past cell Nx - 1 repeat cell Nx - 1.
-//
-// With NT = 512 the two halves of the block solve two tubes (t0, t1; t1 may
-// be -1) side by side: the solve is bound by the latency of its
+// Euler solve of one tube in registers (euler_line) by NT threads of the
+// block.  With NT = 512 the two halves of the block solve two tubes (t0, t1;
+// t1 may be -1) side by side: the solve is bound by the latency of its
 // per-sub-step dependency chain, so two tubes on one compute unit overlap
 // their chains.  Each half has its own LDS region and alpha; the block
 // barrier is shared, so the block runs max(s0, s1) sub-steps and a half
 // that is done only keeps meeting the barrier.
-constexpr int RUN_SLOT = 4;  // doubles per exchanged cell: U, 1/rho
-// LDS of one group of NT threads: per-thread slots [4 cells][RUN_SLOT][NT],
-// the wavefront edge sets [2][NT/64][4 cells][RUN_SLOT] and the wavefront
-// speed maxima [2][NT/64]
-__host__ __device__ constexpr int run_lds_group(int nt) {
-  return 4 * RUN_SLOT * nt + 2 * (nt / 64) * 4 * RUN_SLOT + 2 * (nt / 64);
-}
-constexpr size_t RUN_LDS = (size_t)(2 * run_lds_group(512)) * sizeof(double);
-static_assert(run_lds_group(1024) <= 2 * run_lds_group(512), "one 1024-thread group fits");
+constexpr size_t RUN_LDS = (size_t)2 * LINE_LDS * sizeof(double);
 
 template <int CPT, int NT>
 __device__ void batch_euler_run(const BatchArgs& a, int t0, int t1, double* Lall) {
-  constexpr int WAVES = NT / 64;
   __shared__ int s_grp[2];
   const int grp = (int)threadIdx.x / NT;
-  const int tid = (int)threadIdx.x % NT, lane = tid & 63, wv = tid >> 6;
+  const int tid = (int)threadIdx.x % NT;
   int t = grp == 0 ? t0 : t1;
   t = __builtin_amdgcn_readfirstlane(t);
   if (t >= 0 && a.tflag[t] != 0) t = -1;  // a flagged tube is no longer advanced
@@ -288,174 +215,12 @@ __device__ void batch_euler_run(const BatchArgs& a, int t0, int t1, double* Lall
   __syncthreads();
   const int smax = NT == 1024 ? s : max(s_grp[0], s_grp[1]);
   if (smax == 0) return;
-  const int Nx = G.nc;
-  const int c0 = tid * CPT;          // first cell of the thread
-  const int wfirst = wv * 64 * CPT;  // first cell of the wavefront
-  double* L = Lall + (size_t)grp * run_lds_group(NT);
-  double* SL = L;                          // [4][RUN_SLOT][NT]
-  double* EX = L + 4 * RUN_SLOT * NT;      // [2][WAVES][4][RUN_SLOT]
-  double* WM = EX + 2 * WAVES * 4 * RUN_SLOT;  // [2][WAVES]
-  const double* U0 = a.dar + (p ? T.U[1] : T.U[0]);
-  double U[CPT][3], ir[CPT];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    const bool ok = s > 0 && c0 + j < Nx;  // idle cells hold a finite placeholder
-#pragma unroll
-    for (int r = 0; r < 3; ++r) U[j][r] = ok ? U0[(size_t)r * Nx + c0 + j] : 1.0;
-    ir[j] = rcp_nr(U[j][0]);
-  }
-  // own cells 0, 1 into slots 0, 1 and cells CPT-2, CPT-1 into slots 2, 3;
-  // the wavefront's first two and last two cells into edge set b
-  auto publish = [&](int b) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int j = k < 2 ? k : CPT - 4 + k;
-      if (j < 0 || j >= CPT) continue;
-#pragma unroll
-      for (int r = 0; r < 3; ++r) SL[(k * RUN_SLOT + r) * NT + tid] = U[j][r];
-      SL[(k * RUN_SLOT + 3) * NT + tid] = ir[j];
-    }
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const int q = c0 + j - wfirst;
-      const int slot = q < 2 ? q : (q >= 64 * CPT - 2 ? q - (64 * CPT - 4) : -1);
-      if (slot >= 0) {
-        double* e = EX + ((b * WAVES + wv) * 4 + slot) * RUN_SLOT;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) e[r] = U[j][r];
-        e[3] = ir[j];
-      }
-    }
-  };
-  if (s > 0) publish(0);
-  __syncthreads();
-  const double dts_dx = s > 0 ? (G.dt / s) / G.dx : 0.0;
-  bool phys = true;
-  for (int i = 0; i < smax; ++i) {
-    const int b = i & 1;
-    if (i < s) {
-      if (i > 0) {
-        double m[WAVES];
-#pragma unroll
-        for (int q = 0; q < WAVES; ++q) m[q] = WM[b * WAVES + q];
-#pragma unroll
-        for (int h = WAVES / 2; h >= 1; h /= 2)
-#pragma unroll
-          for (int q = 0; q < h; ++q) m[q] = fmax(m[q], m[q + h]);
-        alpha = m[0];
-      }
-      // split fluxes of an entry from U and 1/rho
-      auto entry = [&](const double* Uq, double irq, double* w) {
-        double F[3];
-        (void)flux1(Uq, irq, F);
-        wsplit(Uq, F, alpha, w);
-      };
-      auto own_entry = [&](int j, double* w) {
-        double F[3];
-        const bool ph = flux1(U[j], ir[j], F);
-        phys &= ph || c0 + j >= Nx;
-        wsplit(U[j], F, alpha, w);
-      };
-      // a neighbour's cell: from its slot k in the thread nb lanes away, or,
-      // past the wavefront's end, from edge slot es of wavefront ew
-      auto remote_entry = [&](int k, int nb, bool edge, int ew, int es, double* w) {
-        const double* src = edge ? EX + ((b * WAVES + ew) * 4 + es) * RUN_SLOT
-                                 : SL + k * RUN_SLOT * NT + (tid + nb);
-        const int stride = edge ? 1 : NT;
-        const double Uq[3] = {src[0], src[stride], src[2 * stride]};
-        entry(Uq, src[3 * stride], w);
-      };
-      // stencil entries k = 0 .. CPT + 3 are the cells c0 - 2 + k: the left
-      // pair from lane - 1's slots 2, 3 (lanes - 2 and - 1 when CPT = 1), the
-      // right pair from lane + 1's slots 0, 1 (lanes + 1 and + 2)
-      auto left_entry = [&](int e, double* w) {
-        const int dl = CPT >= 2 ? 1 : 2 - e;
-        const bool edge = lane < dl;
-        remote_entry(CPT >= 2 ? 2 + e : 0, edge ? 0 : -dl, edge, max(wv - 1, 0),
-                     4 + (c0 - 2 + e - wfirst), w);
-      };
-      auto right_entry = [&](int e, double* w) {
-        const int dr = CPT >= 2 ? 1 : 1 + e;
-        const bool edge = lane >= 64 - dr;
-        remote_entry(CPT >= 2 ? e : 0, edge ? 0 : dr, edge, min(wv + 1, WAVES - 1),
-                     c0 + CPT + e - (wfirst + 64 * CPT), w);
-      };
-      // window of face 0: entries 0 .. 3
-      double W0[6], W1[6], W2[6], W3[6];
-      own_entry(0, W2);
-      left_entry(1, W1);
-      left_entry(0, W0);
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        W1[q] = c0 - 1 < 0 ? W2[q] : W1[q];
-        W0[q] = c0 - 2 < 0 ? W1[q] : W0[q];
-      }
-      if (CPT >= 2)
-        own_entry(CPT >= 2 ? 1 : 0, W3);
-      else
-        right_entry(0, W3);
-      if (c0 + 1 >= Nx) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) W3[q] = W2[q];
-      }
-      double fprev[3];
-      face4(W0, W1, W2, W3, fprev);
-#pragma unroll
-      for (int j = 1; j <= CPT; ++j) {
-        // entry j + 3 (cell c0 + j + 1) enters the window
-        double Wn[6];
-        const int k = j + 3;
-        if (k - 2 < CPT)
-          own_entry(k - 2 < CPT ? k - 2 : 0, Wn);
-        else
-          right_entry(k - 2 - CPT, Wn);
-        const bool past = c0 + j + 1 >= Nx;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          W0[q] = W1[q];
-          W1[q] = W2[q];
-          W2[q] = W3[q];
-          W3[q] = past ? W2[q] : Wn[q];
-        }
-        double fc[3];
-        face4(W0, W1, W2, W3, fc);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) U[j - 1][r] = fma(-dts_dx, fc[r] - fprev[r], U[j - 1][r]);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) fprev[r] = fc[r];
-      }
-      if (i + 1 < s) {
-        // 1/rho and the speeds of the new values; slots, edge cells and
-        // wavefront maxima out before the block barrier
-        double mx = 0.0;
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-          ir[j] = rcp_nr(U[j][0]);
-          double sp;
-          const bool ps = speed1(U[j], ir[j], G.gam, &sp);
-          if (c0 + j < Nx) {
-            phys &= ps;
-            mx = fmax(mx, sp);
-          }
-        }
-        publish(b ^ 1);
-        const double wm = wave_max_dpp(mx);
-        if (lane == 0) WM[(b ^ 1) * WAVES + wv] = wm;
-      }
-    }
-    if (i + 1 < smax) __syncthreads();
-  }
-  if (s == 0) return;
-  double* out = a.dar + ((s & 1) ? T.UE[1] : T.UE[0]);
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    const int c = c0 + j;
-    if (c < Nx) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) out[(size_t)r * Nx + c] = U[j][r];
-    }
-  }
-  if (!phys) atomicOr(a.tflag + t, FLAG_NONPHYS);
+  const double hdts = s > 0 ? 0.5 * ((G.dt / s) / G.dx) : 0.0;
+  const bool phys = euler_line<CPT, false>(
+      a.dar + (p ? T.U[1] : T.U[0]), a.dar + ((s & 1) ? T.UE[1] : T.UE[0]), G.nc, 1,
+      __builtin_amdgcn_readfirstlane(tid >> 6), NT / 64, alpha, s, smax, hdts, G.gam,
+      Lall + (size_t)grp * LINE_LDS);
+  if (s > 0 && !phys) atomicOr(a.tflag + t, FLAG_NONPHYS);
 }
 
 // Euler solve of one part of a tube, cells c0 .. c1-1 with c0 = part * PC
@@ -532,7 +297,7 @@ __device__ void batch_euler_part(const BatchArgs& a, int t, int part, int P, dou
   double Uh[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) Uh[r] = halo ? U0[(size_t)r * Nx + c_h] : 0.0;
-  const double dts_dx = (G.dt / s) / G.dx;
+  const double hdts = 0.5 * ((G.dt / s) / G.dx);
   const int nw = (int)(blockDim.x >> 6);
   bool phys = true;
   for (int i = 0; i < s; ++i) {
@@ -575,9 +340,9 @@ __device__ void batch_euler_part(const BatchArgs& a, int t, int part, int P, dou
       for (int r = 0; r < 3; ++r) {
         const double* wp = Wl + r * WS + f;
         const double* wm = Wl + (3 + r) * WS + f;
-        const double spl = vl_slope_sel(wp[1] - wp[0], wp[2] - wp[1]);
-        const double sml = vl_slope_sel(wm[2] - wm[1], wm[3] - wm[2]);
-        Pl[r * FS + f] = fma(0.25, spl - sml, 0.5 * (wp[1] + wm[2]));
+        const double hp = half_slope<false>(wp[1] - wp[0], wp[2] - wp[1]);
+        const double hm = half_slope<false>(wm[2] - wm[1], wm[3] - wm[2]);
+        Pl[r * FS + f] = face2(wp[1], hp, wm[2], hm);
       }
     }
     __syncthreads();
@@ -588,7 +353,7 @@ __device__ void batch_euler_part(const BatchArgs& a, int t, int part, int P, dou
       const int j = k * 1024 + tid;
 #pragma unroll
       for (int r = 0; r < 3; ++r)
-        Ur[k][r] = fma(-dts_dx, Pl[r * FS + j + 1] - Pl[r * FS + j], Ur[k][r]);
+        Ur[k][r] = fma(-hdts, Pl[r * FS + j + 1] - Pl[r * FS + j], Ur[k][r]);
       if (i + 1 < s) {
         double sp;
         phys &= speed1(Ur[k], rcp_nr(Ur[k][0]), G.gam, &sp);
@@ -835,7 +600,7 @@ __global__ __launch_bounds__(1024) void k_batch_euler(BatchArgs a) {
   double* L = reinterpret_cast<double*>(lds_raw);
   if (e.w == 1) {
     batch_euler_part(a, e.x, e.y, e.z, L, red);
-  } else if (e.w == 2) {  // two tubes of at most 512 * e.z cells side by side
+  } else if (e.w == 2) {  // two tubes of at most 8 line_own(e.z) cells side by side
     if (e.z == 1)
       batch_euler_run<1, 512>(a, e.x, e.y, L);
     else if (e.z == 2)
@@ -846,14 +611,12 @@ __global__ __launch_bounds__(1024) void k_batch_euler(BatchArgs a) {
       batch_euler_run<4, 512>(a, e.x, e.y, L);
   } else {
     const int nx = a.tubes[e.x].Nx;
-    if (nx <= 1024)
-      batch_euler_run<1, 1024>(a, e.x, -1, L);
-    else if (nx <= 2048)
-      batch_euler_run<2, 1024>(a, e.x, -1, L);
-    else if (nx <= 3072)
+    if (nx <= 16 * line_own(3))
       batch_euler_run<3, 1024>(a, e.x, -1, L);
-    else if (nx <= 4096)
+    else if (nx <= 16 * line_own(4))
       batch_euler_run<4, 1024>(a, e.x, -1, L);
+    else if (nx <= 16 * line_own(5))
+      batch_euler_run<5, 1024>(a, e.x, -1, L);
     else
       batch_euler_seg(a, e.x, L, red);
   }

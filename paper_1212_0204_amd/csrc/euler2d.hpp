@@ -11,9 +11,9 @@ namespace hofks {
 // strip of 64 consecutive x cells, of which it advances the inner 60 on H
 // rows (y0 .. y0 + H - 1); lane l is cell X0 - 2 + l.
 //
-// The face flux psi_{j+1/2} = (W+_j + W-_{j+1})/2 + (s+_j - s-_{j+1})/4 is
-// taken as (R_j + L_{j+1})/2, R = W+ + s+/2 and L = W- - s-/2, so that a
-// cell needs two limited slopes per axis and moment instead of four.  Along
+// A limited slope is formed once, by its own cell, so a cell needs two per
+// axis and moment; twice the face flux is (W+_j + W-_{j+1}) + (s+_j - s-_{j+1})/2,
+// rounded as the per-cell form `euler_cell` rounds it.  Along
 // x the neighbours' values come by one-lane shifts of the ALU; along y the
 // wavefront marches over the rows y0 - 2 .. y0 + H + 1 and keeps the last
 // fluxes and half states in registers.  No LDS and no barrier except the
@@ -29,69 +29,50 @@ constexpr int STRIP_W = 60;
 
 // The flux divergence of the H inner rows of a strip: row(q, U) gives the
 // moments of strip row q (0 .. H + 3, the lane's cell) and done(k, div) takes
-// twice the divergence (times dx) of inner row k as soon as it is complete.  Every
-// product and sum of a face is written out, so both cells of a face use the
-// same bits whichever wavefronts form it.
+// twice the divergence (times dx) of inner row k as soon as it is complete.
 template <int H, bool UNL, typename Row, typename Done>
 __device__ __forceinline__ void strip_div(const double* alpha, Row&& row, Done&& done) {
   constexpr int NM = 4;
-  double Wpp[NM] = {}, dP[NM] = {}, Wmp[NM] = {}, dM[NM] = {}, Rp[NM] = {}, Fp[NM] = {};  // last rows
+  // of the last rows; wsum: W+ + W- across the face before row q - 1
+  double Wpp[NM] = {}, dP[NM] = {}, Wmp[NM] = {}, dM[NM] = {}, hpp[NM] = {}, wsum[NM] = {}, Fp[NM] = {};
   double div[H][NM];
 #pragma unroll
   for (int q = 0; q < H + 4; ++q) {
-    double U[NM];
+    double U[NM], Wp[NM], Wm[NM];
     row(q, U);
-    const double rho = U[0], ir = rcp3(rho);
-    const double u = U[1] * ir, v = U[2] * ir;
-    const double usq = fma(u, u, v * v);
-    const double p = 0.5 * fma(-rho, usq, 2.0 * U[3]);  // rho theta
-    const double Ep = U[3] + p;
+    const double ir = rcp_nr(U[0]);
     if (q >= 2 && q < H + 2) {  // x faces of the row
-      const double F[NM] = {U[1], fma(U[1], u, p), U[2] * u, Ep * u};
+      split_flux2(U, ir, 0, alpha[0], Wp, Wm);
 #pragma unroll
       for (int r = 0; r < NM; ++r) {
-        const double wp = fma(alpha[0], U[r], F[r]), wm = fma(-alpha[0], U[r], F[r]);
-        const double dp = lane_next(wp) - wp, dm = lane_next(wm) - wm;
-        const double R = wp + half_slope<UNL>(lane_prev(dp), dp);
-        const double L = wm - half_slope<UNL>(lane_prev(dm), dm);
-        const double f = R + lane_next(L);
+        const double wn = lane_next(Wm[r]);
+        const double dp = lane_next(Wp[r]) - Wp[r], dm = wn - Wm[r];
+        const double hp = half_slope<UNL>(lane_prev(dp), dp);
+        const double hm = half_slope<UNL>(lane_prev(dm), dm);
+        const double f = (Wp[r] + wn) + (hp - lane_next(hm));
         div[q - 2][r] = f - lane_prev(f);
       }
     }
-    const double F[NM] = {U[2], U[1] * v, fma(U[2], v, p), Ep * v};
+    split_flux2(U, ir, 1, alpha[1], Wp, Wm);
 #pragma unroll
     for (int r = 0; r < NM; ++r) {
-      const double wp = fma(alpha[1], U[r], F[r]), wm = fma(-alpha[1], U[r], F[r]);
-      double f = 0.0, R = 0.0;
-      const double dp = wp - Wpp[r], dm = wm - Wmp[r];
-      if (q >= 2 && q < H + 3) R = Wpp[r] + half_slope<UNL>(dP[r], dp);
-      if (q >= 3) {
-        const double L = Wmp[r] - half_slope<UNL>(dM[r], dm);
-        f = Rp[r] + L;  // face between rows q - 2 and q - 1
+      const double dp = Wp[r] - Wpp[r], dm = Wm[r] - Wmp[r];
+      double f = 0.0, hp = 0.0;
+      if (q >= 3) {  // face between rows q - 2 and q - 1
+        f = wsum[r] + (hpp[r] - half_slope<UNL>(dM[r], dm));
         if (q >= 4) div[q - 4][r] += f - Fp[r];
       }
-      Wpp[r] = wp;
-      Wmp[r] = wm;
+      if (q >= 2 && q < H + 3) hp = half_slope<UNL>(dP[r], dp);  // of row q - 1
+      wsum[r] = Wpp[r] + Wm[r];
+      Wpp[r] = Wp[r];
+      Wmp[r] = Wm[r];
       dP[r] = dp;
       dM[r] = dm;
-      Rp[r] = R;
+      hpp[r] = hp;
       Fp[r] = f;
     }
     if (q >= 4) done(q - 4, div[q - 4]);
   }
-}
-
-// whether U is physical, and its speeds |u_a| + c (0 if not)
-__device__ __forceinline__ bool speeds2(const double* U, double gam, double* sp) {
-  const double ir = rcp3(U[0]);
-  const double u = U[1] * ir, v = U[2] * ir;
-  const double sq = fma(u, u, v * v);
-  const double p = 0.5 * fma(-U[0], sq, 2.0 * U[3]);
-  const bool ok = U[0] > 0.0 && p > 0.0 && isfinite(U[0]) && isfinite(p) && isfinite(sq);
-  const double c = ok ? sqrt(gam * p * ir) : 0.0;
-  sp[0] = ok ? fabs(u) + c : 0.0;
-  sp[1] = ok ? fabs(v) + c : 0.0;
-  return ok;
 }
 
 // map_axis for a strip's cells and rows, i >= -2: those past N + 1 are never
@@ -160,12 +141,12 @@ __global__ __launch_bounds__(256) void k_euler_strip(StepArgs<T> a, Geom G, int 
 #pragma unroll
         for (int r = 0; r < NM; ++r) Un[r] = fma(-hdts_dx, div[r], Uc[r]);
         if (!ownx || y >= Ny) return;
-        phys &= i > 0 || speeds2(Uc, G.gam, sp);  // U^n; later inputs were checked as results
+        phys &= i > 0 || speeds2(Uc, rcp_nr(Uc[0]), G.gam, sp);  // U^n; later inputs were checked as results
         const size_t j = (size_t)y * Nx + X0 + lane - 2;
 #pragma unroll
         for (int r = 0; r < NM; ++r) out[(size_t)r * G.nc + j] = Un[r];
         if (i + 1 < s) {
-          phys &= speeds2(Un, G.gam, sp);
+          phys &= speeds2(Un, rcp_nr(Un[0]), G.gam, sp);
           mx[0] = fmax(mx[0], sp[0]);
           mx[1] = fmax(mx[1], sp[1]);
         }

@@ -618,6 +618,26 @@ hofks_status join_update(hofks_ctx* c, const StepArgs<T>& a) {
   return HOFKS_OK;
 }
 
+// Cells per lane and wavefronts of the one-block Euler solve of a 1D grid;
+// false if it does not fit 16 wavefronts.  A sub-step of a wavefront costs
+// about 120 + 150 cpt instructions, at ~6 cycles each while every SIMD holds
+// one wavefront (latency) and ~4.4 per wavefront beyond (FP64 issue).
+bool line_shape(const Plan& P, int* cpt, int* nw) {
+  double best = 0.0;
+  *cpt = 0;
+  for (int k = 1; k <= 4; ++k) {
+    const int w = (P.G.nc + line_own(k) - 1) / line_own(k);
+    if (w > 16) continue;
+    const double cost = ((w + 3) / 4) * (120.0 + 150.0 * k) * (w <= 4 ? 6.0 : 4.4);
+    if (*cpt == 0 || cost < best) {
+      best = cost;
+      *cpt = k;
+      *nw = w;
+    }
+  }
+  return *cpt > 0;
+}
+
 // Rows per strip of the 2D Euler sub-steps.  Short grids want many strips:
 // with one row a sub-step alone takes 5.4 us on 70 x 37 cells and 6.4 on
 // 256^2 (two rows: 6.5 and 6.3, and beside the kinetic kernel 17.5 -> 21.1 on
@@ -644,13 +664,27 @@ int strip_rows(const Plan& P) {
 template <int D, typename T>
 void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
   const Plan& P = c->P;
-  // a 1D grid within one tail block runs every sub-step after the first in
-  // the tail, whose barrier is then the block's own
-  const bool one_block = D == 1 && P.GE == 1 && c->desc.scheme != 3;
-  const int K = std::max(
-      1, std::min(c->s_cap, c->euler_k > 0 ? c->euler_k
-                            : one_block    ? 1
-                                           : c->s_next));
+  if constexpr (D == 1) {
+    int cpt, nw;
+    // In the precision form the records and pieces are rounded to FP32, where
+    // a last bit of the Euler solve can move a result by 1e-8, so while the
+    // pieces carry a part of U^{n+1} (lambda >= 1e-5) it keeps the per-cell
+    // form and its bits.
+    const bool free_bits = !P.prec || P.G.lam < 1e-5;
+    if (c->desc.scheme != 3 && c->euler_k == 0 && free_bits && line_shape(P, &cpt, &nw)) {
+#define KL(C)                                                                                  \
+  if (a.unlimited)                                                                             \
+    hipLaunchKernelGGL((k_euler_line<T, C, true>), dim3(1), dim3(64 * nw), 0, st, a, P.G);     \
+  else                                                                                         \
+    hipLaunchKernelGGL((k_euler_line<T, C, false>), dim3(1), dim3(64 * nw), 0, st, a, P.G)
+      if (cpt == 1) { KL(1); } else if (cpt == 2) { KL(2); } else if (cpt == 3) { KL(3); }
+      else { KL(4); }
+#undef KL
+      return;
+    }
+  }
+  const int K =
+      std::max(1, std::min(c->s_cap, c->euler_k > 0 ? c->euler_k : c->s_next));
   if (c->desc.scheme == 3) {  // WENO: three Runge-Kutta stage launches per sub-step
     if constexpr (D == 2) {  // 16 x 16 LDS tiles
       const int ntx = (P.G.n[0] + WT - 1) / WT, nty = (P.G.n[1] + WT - 1) / WT;
@@ -1668,24 +1702,29 @@ hofks_status batch_order(hofks_ctx* c) {
   std::vector<int> order(B->n);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
-  // whole tubes of at most 2048 cells run two to a block (neighbours in the
+  // whole tubes that fit half a block run two to a block (neighbours in the
   // work order, so of similar work); the others one to a block or in parts
+  auto half_cpt = [&](int i) {
+    int cpt = 1;
+    while (8 * line_own(cpt) < B->tubes[i].Nx) ++cpt;
+    return cpt;
+  };
   std::vector<std::pair<double, int4>> ew;
   int pend = -1;
   for (int i : order) {
     if (parts[i]) {
       for (int k = 0; k < parts[i]; ++k) ew.push_back({work[i], make_int4(i, k, parts[i], 1)});
-    } else if (B->tubes[i].Nx > 2 * 1024) {
+    } else if (B->tubes[i].Nx > 8 * line_own(4)) {
       ew.push_back({work[i], make_int4(i, 0, 0, 0)});
     } else if (pend < 0) {
       pend = i;
     } else {
-      const int cpt = (std::max(B->tubes[pend].Nx, B->tubes[i].Nx) + 511) / 512;
+      const int cpt = std::max(half_cpt(pend), half_cpt(i));
       ew.push_back({std::max(work[pend], work[i]), make_int4(pend, i, cpt, 2)});
       pend = -1;
     }
   }
-  if (pend >= 0) ew.push_back({work[pend], make_int4(pend, -1, (B->tubes[pend].Nx + 511) / 512, 2)});
+  if (pend >= 0) ew.push_back({work[pend], make_int4(pend, -1, half_cpt(pend), 2)});
   std::stable_sort(ew.begin(), ew.end(),
                    [](const std::pair<double, int4>& a, const std::pair<double, int4>& b) {
                      return a.first > b.first;
@@ -1792,7 +1831,10 @@ BatchArgs batch_args(hofks_ctx* c, int parity) {
 }
 
 size_t batch_euler_lds(const Batch* B) {
-  return std::max(std::max(RUN_LDS, EUL_LDS), B->part > 0 ? part_lds(B->part) : (size_t)0);
+  bool seg = false;  // tubes beyond the register form run by segments
+  for (const TubeDev& T : B->tubes) seg = seg || T.Nx > 16 * line_own(5);
+  return std::max(std::max(RUN_LDS, seg ? EUL_LDS : (size_t)0),
+                  B->part > 0 ? part_lds(B->part) : (size_t)0);
 }
 
 // one step: the Euler launch on `stream` and the kinetic launch on the

@@ -27,6 +27,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "slope.hpp"
 
 // stream the pieces with non-temporal loads and stores
 #ifndef HOFKS_EULER_NT
@@ -305,6 +306,46 @@ __device__ __forceinline__ bool lf_speeds(const double* U, double gam, double* s
   const double c = ok ? sqrt(gam * (rho * th) / rho) : 0.0;
 #pragma unroll
   for (int a = 0; a < D; ++a) sp[a] = ok ? fabs(u[a]) + c : 0.0;
+  return ok;
+}
+
+// The same in 2D from U and 1/rho (rcp_nr), for the wavefront strips.  Each
+// rounding is written out where the compiler placed it when the fluxes and
+// faces went through LDS tiles, which the strips replaced, so results kept
+// their bits: quotients by rho and 2 rho are the reciprocal's product
+// corrected by its remainder, which rounds as the division does, and the root
+// is corrected likewise.
+__device__ __forceinline__ void split_flux2(const double* U, double irho, int a, double alpha,
+                                            double* Wp, double* Wm) {
+  const double u[2] = {U[1] * irho, U[2] * irho};
+  const double usq = fma(u[0], u[0], u[1] * u[1]);
+  const double p = fma(2.0, U[3], -(U[0] * usq)) * 0.5;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const double F = r == 0 ? U[1 + a] : fma(U[r], u[a], r == 1 + a ? p : 0.0);
+    Wp[r] = fma(alpha, U[r], F);
+    Wm[r] = fma(-alpha, U[r], F);
+  }
+  const double Ep = U[3] + p, aE = alpha * U[3];
+  Wp[3] = fma(u[a], Ep, aE);
+  Wm[3] = fma(u[a], Ep, -aE);
+}
+
+__device__ __forceinline__ bool speeds2(const double* U, double irho, double gam, double* sp) {
+  const double rho = U[0];
+  auto over = [](double n, double d, double r) {
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+  };
+  const double u = over(U[1], rho, irho), v = over(U[2], rho, irho);
+  const double usq = fma(u, u, v * v);
+  const double th = over(fma(2.0, U[3], -(rho * usq)), 2.0 * rho, 0.5 * irho);
+  const double x = over(gam * (rho * th), rho, irho);
+  // (a sum of positive terms is finite only if each is)
+  const bool ok = (rho > 0.0) && (th > 0.0) && ((rho + th) + (usq + x) < INFINITY);
+  const double c = sqrt_pos(x);
+  sp[0] = ok ? fabs(u) + c : 0.0;
+  sp[1] = ok ? fabs(v) + c : 0.0;
   return ok;
 }
 

@@ -752,3 +752,54 @@ def test_kernel_timing_records_the_masked_groups_only():
     r.set_state_macro(*fields)
     r.step(10)
     assert np.array_equal(r.read_moments(), U)
+
+
+# --------------------------------- Euler solves by wavefront rows and strips
+@gpu
+@pytest.mark.parametrize("nx,bc,scheme,prec", [
+    (1, 1, 0, 0), (2, 0, 0, 0), (3, 1, 2, 0), (5, 0, 2, 0),   # ends within one lane pair
+    (60, 1, 0, 0), (61, 0, 0, 0), (62, 1, 0, 0),              # the seam of two wavefronts
+    (241, 0, 0, 0), (497, 1, 0, 0),                           # two cells a lane, its seams
+    (1009, 0, 2, 0), (2017, 1, 0, 0), (3009, 0, 0, 1),        # three and four cells a lane
+    (4032, 1, 0, 0), (4033, 0, 0, 0),                         # the largest row; past it
+])
+def test_1d_rows_in_one_block(nx, bc, scheme, prec):
+    """the one-block Euler solve of 1D grids at the edges of its wavefronts,
+    lanes and cells per lane; FP32 pieces at lambda < 1e-5"""
+    announce("1d rows", nx, bc, scheme, prec)
+    rng = np.random.default_rng(nx)
+    x = np.linspace(0.0, 2 * np.pi, nx, endpoint=False)
+    rho = 1.0 + 0.15 * np.sin(x) + 0.05 * rng.uniform(-1, 1, nx)
+    th = 1.0 + 0.1 * np.cos(x) + 0.05 * rng.uniform(-1, 1, nx)
+    u = 0.1 * np.sin(x)[None]
+    dx = 1.0 / max(nx, 16)
+    nv = 16 if bc else min(16, 2 * nx)  # a periodic axis holds the largest shift
+    dv = 8.0 / nv
+    o, s = run_pair(1, (nx,), dx, nv, dv, (bc,), 0.05 * dx / dv, 3, (rho, u, th),
+                    precision=prec, scheme=scheme)
+    err = moment_errors(s.read_moments(), o.U, 1)
+    assert err.max() < (TOL64 if prec == 0 else TOL32), err
+    assert s.counters()[0] == o.substeps
+
+
+@gpu
+@pytest.mark.parametrize("n,bc,scheme", [
+    ((1, 5), (1, 0), 0), ((2, 2), (1, 0), 0), ((3, 1), (1, 0), 0),   # thinner than a stencil
+    ((60, 4), (0, 0), 0), ((61, 9), (1, 1), 2), ((59, 3), (0, 1), 0),  # strip seams, ragged rows
+    ((130, 331), (1, 0), 0),     # three strips, one row each
+    ((470, 300), (0, 0), 0),     # more strips than compute units: several rows
+])
+def test_2d_strips(n, bc, scheme):
+    """the wavefront strips of the 2D Euler solve at their seams and on axes
+    of fewer cells than the stencil"""
+    announce("2d strips", n, bc, scheme)
+    rng = np.random.default_rng(n[0] + n[1])
+    nc = n[0] * n[1]
+    rho = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    th = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    u = 0.1 * rng.uniform(-1, 1, (2, nc))
+    dx = 1.0 / max(n)
+    o, s = run_pair(2, n, dx, 8, 0.75, bc, 0.2 * dx, 2, (rho, u, th), scheme=scheme)
+    err = moment_errors(s.read_moments(), o.U, 2)
+    assert err.max() < TOL64, err
+    assert s.counters()[0] == o.substeps

@@ -636,4 +636,26 @@ __global__ __launch_bounds__(1024) void k_batch_update(BatchArgs a) {
   batch_update_item(a, blockIdx.x);
 }
 
+// Initial state of every tube in one launch: block (x, y) takes 256 cells of
+// tube y.  prim: rho, u and theta of all tubes (ncells values each, in tube
+// order); a tube's first cell is its offset in the U^n array over 3.
+__global__ __launch_bounds__(256) void k_batch_set(BatchArgs a, const double* prim, size_t ncells) {
+  const int t = blockIdx.y;
+  const TubeDev T = a.tubes[t];
+  const int x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if ((int)(blockIdx.x * blockDim.x) >= T.Nx) return;
+  const Geom G = tube_geom(T);
+  Mat A;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) A.a[q] = T.A[q];
+  bool phys = true;
+  double speed[3] = {0.0, 0.0, 0.0};
+  if (x < T.Nx)
+    phys = set_state_cell<1, float>(prim + T.U[0] / 3 + x, ncells, x, G, A, a.gar + T.g[0],
+                                    a.dar + T.U[0], a.dar + T.cf, a.rar + T.rec[0], speed);
+  if (!phys) atomicOr(a.tflag + t, FLAG_NONPHYS);
+  const double m = wave_max(phys ? speed[0] : 0.0);
+  if ((threadIdx.x & 63) == 0) atomic_max_pos(a.alpha + (size_t)t * 2 * ASTR, m);
+}
+
 }  // namespace hofks

@@ -1205,26 +1205,20 @@ hofks_status hofks_set_state_macro(hofks_ctx* c, const double* rho, const double
   HIPCHK(c, hipMemcpyAsync(prim, rho, nc * 8, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(prim + nc, u, nc * 8 * P.d, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(prim + nc * (P.d + 1), theta, nc * 8, hipMemcpyHostToDevice, c->stream));
-  st = zero_doubles(c, c->cf, (size_t)P.nm * nc);
-  if (st) return st;
   st = dispatch(c, [&](auto D, auto t) -> hofks_status {
     constexpr int DD = decltype(D)::value;
     using T = decltype(t);
-    hipLaunchKernelGGL((k_prim_to_moments<DD>), dim3(nblk(nc)), dim3(256), 0, c->stream, prim,
-                       c->U[0], (int)nc);
-    // Maxwellian parameters of U^0, then sample M into the pieces, sum the
-    // stored pieces and project onto U^0 (f^0 = E[U^0], section 4.2)
-    hofks_status s2 = launch_cell_init<DD, T>(c, MODE_REFRESH);
-    if (s2) return s2;
-    const size_t tot = (size_t)P.G.nv * nc;
-    hipLaunchKernelGGL((k_fill_maxwellian<DD, T>), dim3(nblk(tot)), dim3(256), 0, c->stream,
-                       (T*)c->g[0], (const T*)c->rec[0], P.G);
-    hipLaunchKernelGGL((k_piece_sums<DD, T>), dim3(nblk(nc)), dim3(256), 0, c->stream,
-                       (const T*)c->g[0], c->part, P.G);
+    Geom Gi = P.G;  // the records formed here are read by the next step
+    Gi.lam_r = Gi.lam;
+    Gi.mu_r = Gi.mu;
+    // a wavefront per block until every SIMD has one: the cells' loops over the
+    // velocities are long, so few cells are spread over many compute units
+    const unsigned tpb = nc <= (size_t)P.ncu * 256 ? 64 : 256;
+    hipLaunchKernelGGL((k_set_state<DD, T>), dim3(nblk(nc, tpb)), dim3(tpb), 0, c->stream, prim,
+                       (T*)c->g[0], c->U[0], c->cf, (T*)c->rec[0], slot_set(c, rset(c)), c->flag,
+                       Gi, P.A);
     HIPCHK(c, hipGetLastError());
-    s2 = zero_doubles(c, c->slots, 3 * (size_t)SET_D);
-    if (s2) return s2;
-    return launch_cell_init<DD, T>(c, MODE_INIT);
+    return HOFKS_OK;
   });
   if (st) return st;
   c->ready = true;
@@ -1571,14 +1565,8 @@ hofks_status batch_plan(const hofks_grid_desc* descs, const double* taus, int n,
     T.rec[0] = ro;
     T.rec[1] = ro + RS * Nx;
     ro += 2 * RS * Nx;
-    T.U[0] = dof;
-    T.U[1] = dof + 3 * Nx;
-    T.UE[0] = dof + 6 * Nx;
-    T.UE[1] = dof + 9 * Nx;
-    T.cf = dof + 12 * Nx;
-    T.S = dof + 15 * Nx;
-    T.X = dof + 21 * Nx;
-    dof += 21 * Nx + 2LL * XSTR * ((Nx + 1023) / 1024);
+    T.U[0] = dof;  // (the other moment arrays follow below)
+    dof += 3 * Nx;
     T.vt = vto;
     vto += (int)nv;
     T.Nx = (int)Nx;
@@ -1604,6 +1592,19 @@ hofks_status batch_plan(const hofks_grid_desc* descs, const double* taus, int n,
     eitems += (int)((Nx + 1023) / 1024);
     B->total_cells += Nx;
     B->total_cv += Nx * nv;
+  }
+  // moment arrays one after another, each holding all tubes in order, so that
+  // a state is handed over and the moments read in one copy per array
+  const long long C3 = dof;
+  dof *= 7;
+  for (TubeDev& T : B->tubes) {
+    T.U[1] = T.U[0] + C3;
+    T.UE[0] = T.U[0] + 2 * C3;
+    T.UE[1] = T.U[0] + 3 * C3;
+    T.cf = T.U[0] + 4 * C3;
+    T.S = 5 * C3 + 2 * T.U[0];
+    T.X = dof;
+    dof += 2LL * XSTR * ((T.Nx + 1023) / 1024);
   }
   B->g_floats = go;
   B->r_floats = ro;
@@ -1970,41 +1971,23 @@ hofks_status batch_set_state(hofks_ctx* c, const double* rho, const double* u,
   if (st) return st;
   st = zero_doubles(c, B->alpha, (size_t)B->n * 2 * ASTR);
   if (st) return st;
-  long long cell0 = 0;
-  for (int i = 0; i < B->n; ++i) {
-    const TubeDev& T = B->tubes[i];
-    const Geom G = host_tube_geom(T);
-    Mat A;
-    for (int q = 0; q < 9; ++q) A.a[q] = T.A[q];
-    const size_t nx = T.Nx;
-    double* prim = B->dar + T.UE[0];  // rho | u | theta staging (3 x Nx)
-    double* U0 = B->dar + T.U[0];
-    double* cf = B->dar + T.cf;
-    double* part = B->dar + T.UE[1];
-    float* rec0 = B->rar + T.rec[0];
-    float* g0 = B->gar + T.g[0];
-    const VelNode* vt = B->vtar + T.vt;
-    double* al = B->alpha + (size_t)i * 2 * ASTR;
-    HIPCHK(c, hipMemcpyAsync(prim, rho + cell0, nx * 8, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(prim + nx, u + cell0, nx * 8, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(prim + 2 * nx, theta + cell0, nx * 8, hipMemcpyHostToDevice, c->stream));
-    st = zero_doubles(c, cf, 3 * nx);
-    if (st) return st;
-    hipLaunchKernelGGL((k_prim_to_moments<1>), dim3(nblk(nx)), dim3(256), 0, c->stream, prim, U0,
-                       (int)nx);
-    hipLaunchKernelGGL((k_cell_init<1, float>), dim3(nblk(nx)), dim3(256), 0, c->stream, U0, cf,
-                       rec0, vt, part, al, B->tflag + i, G, A, (int)MODE_REFRESH);
-    hipLaunchKernelGGL((k_fill_maxwellian<1, float>), dim3(nblk(nx * T.nv1)), dim3(256), 0,
-                       c->stream, g0, (const float*)rec0, G);
-    hipLaunchKernelGGL((k_piece_sums<1, float>), dim3(nblk(nx)), dim3(256), 0, c->stream,
-                       (const float*)g0, part, G);
-    st = zero_doubles(c, al, ASTR);
-    if (st) return st;
-    hipLaunchKernelGGL((k_cell_init<1, float>), dim3(nblk(nx)), dim3(256), 0, c->stream, U0, cf,
-                       rec0, vt, part, al, B->tflag + i, G, A, (int)MODE_INIT);
-    HIPCHK(c, hipGetLastError());
-    cell0 += (long long)nx;
+  const size_t nc = (size_t)B->total_cells;
+  double* prim = B->dar + B->tubes[0].UE[0];  // rho | u | theta of all tubes
+  HIPCHK(c, hipMemcpyAsync(prim, rho, nc * 8, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(prim + nc, u, nc * 8, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(prim + 2 * nc, theta, nc * 8, hipMemcpyHostToDevice, c->stream));
+  int nx_max = 0;
+  for (const TubeDev& T : B->tubes) nx_max = std::max(nx_max, T.Nx);
+  const BatchArgs a = batch_args(c, 0);
+  for (int t0 = 0; t0 < B->n; t0 += 65535) {  // grid.y limit
+    BatchArgs at = a;
+    at.tubes += t0;
+    at.tflag += t0;
+    at.alpha += (size_t)t0 * 2 * ASTR;
+    hipLaunchKernelGGL(k_batch_set, dim3(nblk(nx_max), std::min(65535, B->n - t0)), dim3(256), 0,
+                       c->stream, at, (const double*)prim, nc);
   }
+  HIPCHK(c, hipGetLastError());
   c->ready = true;
   st = batch_order(c);
   if (st) return st;
@@ -2345,12 +2328,8 @@ namespace {
 hofks_status batch_read_moments(hofks_ctx* c, double* U) {
   Batch* B = c->batch;
   const int p = (int)(c->steps & 1);
-  long long o = 0;
-  for (const TubeDev& T : B->tubes) {
-    HIPCHK(c, hipMemcpyAsync(U + o, B->dar + T.U[p], sizeof(double) * 3 * T.Nx,
-                             hipMemcpyDeviceToHost, c->stream));
-    o += 3LL * T.Nx;
-  }
+  HIPCHK(c, hipMemcpyAsync(U, B->dar + B->tubes[0].U[p], sizeof(double) * 3 * B->total_cells,
+                           hipMemcpyDeviceToHost, c->stream));
   return batch_read_flag(c);
 }
 

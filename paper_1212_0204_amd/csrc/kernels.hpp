@@ -70,8 +70,7 @@ struct Mat {
   double a[25];
 };
 
-// MODE_RETAU: as MODE_REFRESH, keeping the mark of cells without pieces
-enum { MODE_STEP = 0, MODE_INIT = 1, MODE_INIT_FROM_SUMS = 2, MODE_REFRESH = 3, MODE_RETAU = 4 };
+enum { MODE_INIT_FROM_SUMS = 2, MODE_RETAU = 4 };
 
 // ------------------------------------------------------------------ helpers
 __device__ __forceinline__ int map_axis(int i, int N, int bc) {
@@ -1390,11 +1389,10 @@ __global__ __launch_bounds__(256) void k_cell_record(StepArgs<T> a, Geom G, Mat 
 }
 
 // ======================================================= set-up / refresh
-// MODE_INIT: U given, the pieces g hold sampled values with sums S (chunk 0
-// of part): project onto U as in eq. (minim1), cf = A (U - w S).
-// MODE_INIT_FROM_SUMS: U = w S (cf = 0).  MODE_REFRESH: U and cf given
-// (after a change of tau).  Writes the record and the speeds of U (row 0 of
-// `set`).
+// MODE_INIT_FROM_SUMS: U = w S with the sums S of the pieces (chunk 0 of
+// part), cf = A (U - w S).  MODE_RETAU: U and cf given (after a change of tau),
+// the marks of cells without pieces kept.  Writes the record and the speeds
+// of U (row 0 of `set`).
 template <int D, typename T>
 __global__ __launch_bounds__(256) void k_cell_init(double* __restrict__ U, double* __restrict__ cf,
                                                    T* __restrict__ rec,
@@ -1410,7 +1408,7 @@ __global__ __launch_bounds__(256) void k_cell_init(double* __restrict__ U, doubl
   double speed[3] = {0.0, 0.0, 0.0};
   if (act) {
     double Un[NM], cfv[NM];
-    if (mode == MODE_REFRESH || mode == MODE_RETAU) {
+    if (mode == MODE_RETAU) {
 #pragma unroll
       for (int r = 0; r < NM; ++r) {
         Un[r] = U[(size_t)r * G.nc + j];
@@ -1421,7 +1419,7 @@ __global__ __launch_bounds__(256) void k_cell_init(double* __restrict__ U, doubl
 #pragma unroll
       for (int r = 0; r < NM; ++r) {
         S[r] = part[(size_t)r * G.nc + j];
-        Un[r] = (mode == MODE_INIT) ? U[(size_t)r * G.nc + j] : G.w * S[r];
+        Un[r] = G.w * S[r];
       }
 #pragma unroll
       for (int r = 0; r < NM; ++r) {
@@ -1439,7 +1437,7 @@ __global__ __launch_bounds__(256) void k_cell_init(double* __restrict__ U, doubl
       cf[(size_t)r * G.nc + j] = cfv[r];
     }
   }
-  if (act && (G.mu != 0.0 || mode == MODE_INIT) && !phys) atomicOr(flag, FLAG_NONPHYS);
+  if (act && G.mu != 0.0 && !phys) atomicOr(flag, FLAG_NONPHYS);
 #pragma unroll
   for (int d2 = 0; d2 < D; ++d2) {
     const double m = wave_max(phys ? speed[d2] : 0.0);
@@ -1448,41 +1446,139 @@ __global__ __launch_bounds__(256) void k_cell_init(double* __restrict__ U, doubl
 }
 
 // ============================================================ set-up kernels
-template <int D>
-__global__ void k_prim_to_moments(const double* __restrict__ prim, double* __restrict__ U,
-                                  int nc) {
-  constexpr int NM = D + 2;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= nc) return;
-  const double rho = prim[j], th = prim[(size_t)(D + 1) * nc + j];
-  double usq = 0.0;
-  U[j] = rho;
+// Initial state of one cell (section 4.2) in one pass: U^0 from (rho, u,
+// theta), the Maxwellian of U^0 sampled into the cell's pieces (parameters in
+// the record's precision), the sums S of the stored pieces, and the
+// projection onto U^0, cf = A (U^0 - w S), with the record and the speeds.  The
+// pieces of a cell are formed and summed by one thread in the order of k, eight
+// exponentials ahead, so that the pieces are written once and never read: bound
+// by the FP64 exponentials (the separate passes also read every piece back,
+// one load at a time, and divided indexes per piece).
+template <int D, typename T>
+__device__ __forceinline__ bool set_state_cell(const double* __restrict__ prim, size_t pstride,
+                                               int j, const Geom& G, const Mat& A,
+                                               T* __restrict__ g, double* __restrict__ U,
+                                               double* __restrict__ cf, T* __restrict__ rec,
+                                               double* speed) {
+  constexpr int NM = D + 2, AHEAD = 8;
+  constexpr int RS = rec_stride<D, T>();
+  const double rho = prim[0], th0 = prim[(size_t)(D + 1) * pstride];
+  double Un[NM], usq0 = 0.0;
+  Un[0] = rho;
 #pragma unroll
   for (int a = 0; a < D; ++a) {
-    const double ua = prim[(size_t)(1 + a) * nc + j];
-    U[(size_t)(1 + a) * nc + j] = rho * ua;
-    usq += ua * ua;
+    const double ua = prim[(size_t)(1 + a) * pstride];
+    Un[1 + a] = rho * ua;
+    usq0 += ua * ua;
   }
-  U[(size_t)(NM - 1) * nc + j] = 0.5 * rho * usq + 0.5 * D * rho * th;
+  Un[NM - 1] = 0.5 * rho * usq0 + 0.5 * D * rho * th0;
+  // parameters of the Maxwellian of U^0, as in the record
+  double u[3] = {0.0, 0.0, 0.0}, usq = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    u[a] = Un[1 + a] / rho;
+    usq += u[a] * u[a];
+  }
+  const double th = (2.0 * Un[NM - 1] - rho * usq) / (D * rho);
+  const bool phys = (rho > 0.0) && (th > 0.0) && isfinite(rho) && isfinite(th) && isfinite(usq);
+  double lp = 0.0, beta = 0.0;
+  if (phys) {
+    beta = 0.5 / th;
+    lp = log(rho) - 0.5 * D * log(2.0 * M_PI * th);
+  }
+  lp = (double)(T)lp;
+  beta = (double)(T)beta;
+#pragma unroll
+  for (int a = 0; a < D; ++a) u[a] = (double)(T)u[a];
+
+  double S[NM];
+#pragma unroll
+  for (int r = 0; r < NM; ++r) S[r] = 0.0;
+  const int nrow = D == 1 ? 1 : D == 2 ? G.nv1 : G.nv1 * G.nv1;
+  for (int row = 0; row < nrow; ++row) {
+    const double vy = (row % G.nv1 - G.kofs) * G.dv, vz = (row / G.nv1 - G.kofs) * G.dv;
+    T* gr = g + (size_t)row * G.nv1 * G.nc + j;
+    for (int i0 = 0; i0 < G.nv1; i0 += AHEAD) {
+      double val[AHEAD];
+#pragma unroll
+      for (int e = 0; e < AHEAD; ++e) {
+        const double vx = (i0 + e - G.kofs) * G.dv;
+        double q = 0.0;
+        const double dx = vx - u[0];
+        q += dx * dx;
+        if (D >= 2) {
+          const double dy = vy - u[1];
+          q += dy * dy;
+        }
+        if (D >= 3) {
+          const double dz = vz - u[2];
+          q += dz * dz;
+        }
+        val[e] = (double)(T)exp(lp - beta * q);
+      }
+#pragma unroll
+      for (int e = 0; e < AHEAD; ++e) {
+        if (i0 + e < G.nv1) {
+          const double vx = (i0 + e - G.kofs) * G.dv;
+          gr[(size_t)(i0 + e) * G.nc] = (T)val[e];
+          double vsq = 0.0;
+          S[0] += val[e];
+          S[1] += vx * val[e];
+          vsq += vx * vx;
+          if (D >= 2) {
+            S[2] += vy * val[e];
+            vsq += vy * vy;
+          }
+          if (D >= 3) {
+            S[NM - 2] += vz * val[e];
+            vsq += vz * vz;
+          }
+          S[NM - 1] += 0.5 * vsq * val[e];
+        }
+      }
+    }
+  }
+  double cfv[NM];
+#pragma unroll
+  for (int r = 0; r < NM; ++r) {
+    double acc = 0.0;
+#pragma unroll
+    for (int s2 = 0; s2 < NM; ++s2) acc += A.a[r * NM + s2] * (Un[s2] - G.w * S[s2]);
+    cfv[r] = acc;
+  }
+  const bool ok = cell_record<D, T>(Un, cfv, G, A, rec + (size_t)j * RS, speed, true);
+#pragma unroll
+  for (int r = 0; r < NM; ++r) {
+    U[(size_t)r * G.nc + j] = Un[r];
+    cf[(size_t)r * G.nc + j] = cfv[r];
+  }
+  return phys && ok;
 }
 
-// g(j,k) = M_k of cell j (the pointwise Maxwellian of the record)
+// the initial state of a grid, one cell per thread; speeds to row 0 of `set`
 template <int D, typename T>
-__global__ void k_fill_maxwellian(T* __restrict__ g, const T* __restrict__ rec, Geom G) {
-  constexpr int RS = rec_stride<D, T>();
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)G.nv * G.nc) return;
-  const int j = (int)(idx % G.nc);
-  int k = (int)(idx / G.nc);
-  double q = 0.0;
+__global__ __launch_bounds__(256) void k_set_state(const double* __restrict__ prim,
+                                                   T* __restrict__ g, double* __restrict__ U,
+                                                   double* __restrict__ cf, T* __restrict__ rec,
+                                                   double* __restrict__ set, int* __restrict__ flag,
+                                                   Geom G, Mat A) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  bool phys = true;
+  double speed[3] = {0.0, 0.0, 0.0};
+  if (j < G.nc) phys = set_state_cell<D, T>(prim + j, G.nc, j, G, A, g, U, cf, rec, speed);
+  if (!phys) atomicOr(flag, FLAG_NONPHYS);
+  __shared__ double wm[4][ASTR];
 #pragma unroll
-  for (int a = 0; a < D; ++a) {
-    const double v = (k % G.nv1 - G.kofs) * G.dv;
-    k /= G.nv1;
-    const double d = v - (double)rec[(size_t)j * RS + 1 + a];
-    q += d * d;
+  for (int d2 = 0; d2 < D; ++d2) {
+    const double m = wave_max(phys ? speed[d2] : 0.0);
+    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6][d2] = m;
   }
-  g[idx] = (T)exp((double)rec[(size_t)j * RS] - (double)rec[(size_t)j * RS + D + 1] * q);
+  __syncthreads();
+  if (threadIdx.x < D) {
+    double m = wm[0][threadIdx.x];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmax(m, wm[w][threadIdx.x]);
+    atomic_max_pos(set + threadIdx.x, m);
+  }
 }
 
 // S_r(j) = sum_k m_k[r] g(j,k) into part chunk 0

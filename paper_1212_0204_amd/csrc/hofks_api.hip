@@ -485,12 +485,33 @@ size_t kin2w_lds(const Plan& P, int ng) {
   return std::max(stage, red);
 }
 
+// LDS to ask for so that a compute unit takes no more blocks than its even
+// share of a launch of nb blocks.  A launch of one round is as long as its
+// fullest compute unit, and where Euler blocks sit when it is dispatched the
+// others would take its blocks, up to what fits: with room for three blocks
+// and a share of two the off-lattice 256^2 kinetic launch took 217 or 270 us
+// as the Euler blocks left before or after its dispatch.
+size_t even_lds(const Plan& P, size_t lds, unsigned nb) {
+  constexpr size_t CU = 160 * 1024;
+  const size_t share = (nb + P.ncu - 1) / P.ncu;
+  const size_t pad = CU / (share + 1) + 512;  // share + 1 of these do not fit
+  return pad > lds && pad <= 65536 && pad * share <= CU ? pad : lds;
+}
+
 void dispatch_kin2w(hofks_ctx* c, const StepArgs<double>& a) {
   const Plan& P = c->P;
   const int nsegw = (P.G.n[0] + W2_CELLS - 1) / W2_CELLS;
   const dim3 grid((unsigned)((long)nsegw * P.G.n[1]));
+  if (P.G.offl) {
+    const size_t lds4 = even_lds(P, kin2w_lds(P, 4), grid.x);
+    if (P.G.bc[0] == 0)
+      hipLaunchKernelGGL((k_kinetic2w<0, 4, 4, true>), grid, dim3(256), lds4, c->stream, a, P.G, nsegw);
+    else
+      hipLaunchKernelGGL((k_kinetic2w<1, 4, 4, true>), grid, dim3(256), lds4, c->stream, a, P.G, nsegw);
+    return;
+  }
   const int ng = c->kng == 2 ? 2 : 4, unr = P.G.nv1 % 8 == 0 && c->kunr == 8 ? 8 : 4;
-  const size_t lds = kin2w_lds(P, ng);
+  const size_t lds = even_lds(P, kin2w_lds(P, ng), grid.x);
 #define K(BCX, NG, U)                                                                    \
   hipLaunchKernelGGL((k_kinetic2w<BCX, U, NG>), grid, dim3(64 * NG), lds, c->stream, a, \
                      P.G, nsegw)
@@ -516,7 +537,8 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
     }
   }
   if constexpr (D == 2 && EUL && !FT && sizeof(T) == 8) {
-    if (c->kwide) {
+    // (off the lattice as well: there in one configuration, whatever is set)
+    if (c->kwide || (P.G.offl && P.G.nv1 <= W2_OFFL_NV && kin2w_lds(P, 4) <= 65536)) {
       dispatch_kin2w(c, a);
       return;
     }

@@ -22,7 +22,13 @@ namespace hofks {
 constexpr int W2_CELLS = 128;  // cells per block row segment
 typedef double w2v __attribute__((ext_vector_type(2)));  // a lane's two pieces
 
-template <int BCX, int UNR, int NG>
+// OFFL: a free time step; the shift of a velocity node in this step replaces
+// its lattice shift (formed once per block, read from LDS as scalars).  256^2 x 32^2 at kinetic CFL 1: the
+// launch 0.216 ms (5.0 TB/s) against 0.244 with one cell per lane, the step
+// 0.262 -> 0.236 ms.
+constexpr int W2_OFFL_NV = 128;  // most nodes per axis then
+
+template <int BCX, int UNR, int NG, bool OFFL = false>
 __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom G, int nsegw) {
   using T = double;
   constexpr int NM = 4;
@@ -51,6 +57,14 @@ __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom 
   const int xlo = x0 - lofs;
   const T lam = (T)G.lam, mu = (T)G.mu;
   const int nvr = G.nv1;
+  __shared__ int shs[OFFL ? W2_OFFL_NV : 1];
+  if (OFFL) {
+    for (int i = threadIdx.x; i < nvr; i += 64 * NG) shs[i] = node_shift(a.vt, i, G, a.nstep);
+    __syncthreads();
+  }
+  auto shift = [&](int i) {  // cells that pieces of node i (scalar) move
+    return OFFL ? __builtin_amdgcn_readfirstlane(shs[OFFL ? i : 0]) : i - G.kofs;
+  };
   const int vr0 = grp * nvr / NG, vr1 = (grp + 1) * nvr / NG;
   T* Lw = lds + (size_t)grp * 2 * SP * FS;
 
@@ -62,7 +76,7 @@ __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom 
 
   for (int vr = vr0; vr < vr1; ++vr) {
     const int iy = vr;
-    const int ky = iy - G.kofs;
+    const int ky = shift(iy);
     const double vy = vel_node(a.vt, iy).v;
     const double hrow = vel_node(a.vt, iy).v2h;
     const int uy = map_axis(jy - ky, G.n[1], G.bc[1]);
@@ -106,7 +120,7 @@ __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom 
       w2v gv[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        const int kx = ix0 + u - G.kofs;
+        const int kx = shift(ix0 + u);
         const char* gp = reinterpret_cast<const char*>(a.g_in + (kbase + ix0 + u) * (size_t)G.nc) +
                          (size_t)ubase * sizeof(T);
         // upstream cells of the pair, mapped as the single-cell form does
@@ -125,7 +139,7 @@ __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom 
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         const int ix = ix0 + u;
-        const int kx = ix - G.kofs;
+        const int kx = shift(ix);
         const VelNode vn = vel_node(a.vt, ix);
         const T vxT = (T)vn.v;
         const T vhT = (T)vn.v2h;

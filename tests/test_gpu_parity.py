@@ -803,3 +803,31 @@ def test_2d_strips(n, bc, scheme):
     err = moment_errors(s.read_moments(), o.U, 2)
     assert err.max() < TOL64, err
     assert s.counters()[0] == o.substeps
+
+
+@gpu
+@pytest.mark.parametrize("n,nv,bc,frac", [
+    ((127, 5), 16, (0, 0), 0.11),    # one odd segment of pairs
+    ((129, 4), 12, (1, 0), 0.73),    # a pair past the first segment, outflow clamps
+    ((260, 3), 72, (0, 1), 0.037),   # more than 64 nodes an axis
+    ((60, 7), 4, (1, 1), 1.0),       # fewest nodes; dt = dx/dv given explicitly
+])
+def test_2d_offlattice_pairs(n, nv, bc, frac):
+    """off-lattice transport in the two-cell kernel: odd widths, segment seams
+    and many nodes"""
+    announce("2d off-lattice pairs", n, nv, bc, frac)
+    from paper_1212_0204_amd import Solver
+    rng = np.random.default_rng(nv)
+    nc = n[0] * n[1]
+    dx, dv = 1.0 / n[0], 8.0 / nv
+    dt = frac * dx / dv
+    fields = (1.0 + 0.1 * rng.uniform(-1, 1, nc), 0.1 * rng.uniform(-1, 1, (2, nc)),
+              1.0 + 0.1 * rng.uniform(-1, 1, nc))
+    o = Oracle(2, n, dx, nv, dv, bc=bc, tau=0.5 * dt, dt=dt)
+    s = Solver(2, n, dx, nv, dv, bc=bc, tau=0.5 * dt, dt=dt)
+    o.init_macro(*fields)
+    s.set_state_macro(*fields)
+    o.step(7)
+    s.step(7)
+    assert moment_errors(s.read_moments(), o.U, 2).max() < TOL64
+    assert rel_inf(s.read_f(), o.f) < TOL64

@@ -75,12 +75,46 @@ __device__ __forceinline__ void strip_div(const double* alpha, Row&& row, Done&&
   }
 }
 
-// map_axis for a strip's cells and rows, i >= -2: those past N + 1 are never
-// used and taken as N + 1, and an axis of two cells or more needs no division
+// map_axis for a strip's cells and rows, i >= -HALO: those past N + HALO - 1
+// are never used and taken as that, and an axis of HALO cells or more needs no
+// division
+template <int HALO>
 __device__ __forceinline__ int map_near(int i, int N, int bc) {
-  i = min(i, N + 1);
-  if (bc == 0 && N >= 2) return i < 0 ? i + N : (i >= N ? i - N : i);
+  i = min(i, N + HALO - 1);
+  if (bc == 0 && N >= HALO) return i < 0 ? i + N : (i >= N ? i - N : i);
   return map_axis(i, N, bc);
+}
+
+// speeds of row i of a 2D set: lane 4 q + d reads axis d of slot q (row 0 has
+// one slot); every lane of the wavefront takes part
+__device__ __forceinline__ void strip_speeds(const double* S, int i, int lane, double* alpha) {
+  if (i == 0) {
+    const double al = S[lane & 1];
+    alpha[0] = lane_value(al, 0);
+    alpha[1] = lane_value(al, 1);
+    return;
+  }
+  double al = S[ASTR + (size_t)(i - 1) * NSLOT * ASTR + (lane & 31)];
+  al = dpp_max<0x114, 0xF>(al);  // lanes 4..: max with lane - 4
+  al = dpp_max<0x118, 0xF>(al);  // lanes 12..15: the row's four slots
+  alpha[0] = fmax(lane_value(al, 12), lane_value(al, 28));
+  alpha[1] = fmax(lane_value(al, 13), lane_value(al, 29));
+}
+
+// the largest speeds of a block of four strips into row i of the set
+__device__ __forceinline__ void fold_speeds(double* S, int i, int lane, int wv, const double* mx) {
+  __shared__ double wm4[2][4];
+#pragma unroll
+  for (int d2 = 0; d2 < 2; ++d2) {
+    const double m = wave_max_dpp(mx[d2]);
+    if (lane == 0) wm4[d2][wv] = m;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const double* m = wm4[threadIdx.x];
+    atomic_max_pos(speed_row(S, i, blockIdx.x % NSLOT) + threadIdx.x,
+                   fmax(fmax(m[0], m[1]), fmax(m[2], m[3])));
+  }
 }
 
 template <typename T, int H, bool UNL>
@@ -98,31 +132,19 @@ __global__ __launch_bounds__(256) void k_euler_strip(StepArgs<T> a, Geom G, int 
 
   // every row of the strip, loaded before the speeds of the sub-step are
   // read so that the memory round trips overlap
-  const int gx = map_near(X0 - 2 + lane, Nx, G.bc[0]);
+  const int gx = map_near<2>(X0 - 2 + lane, Nx, G.bc[0]);
   double Ur[H + 4][NM];
 #pragma unroll
   for (int q = 0; q < H + 4; ++q) {
-    const size_t j = (size_t)map_near(y0 - 2 + q, Ny, G.bc[1]) * Nx + gx;
+    const size_t j = (size_t)map_near<2>(y0 - 2 + q, Ny, G.bc[1]) * Nx + gx;
 #pragma unroll
     for (int r = 0; r < NM; ++r) Ur[q][r] = in[(size_t)r * G.nc + j];
   }
-  // speeds of the sub-step: lane 4 q + d reads axis d of slot q (row 0 has
-  // one slot)
-  const double* sp_row = S + (i == 0 ? 0 : ASTR + (size_t)(i - 1) * NSLOT * ASTR);
-  double al = sp_row[i == 0 ? lane & 1 : (lane & 31)];
+  double alpha[2];
+  strip_speeds(S, i, lane, alpha);
   // the count: formed by sub-step 0, which records it for the later launches
   const int s = i == 0 ? open_substeps<2>(a, G) : a.flag[1];
   if (i >= s) return;
-  double alpha[2];
-  if (i == 0) {
-    alpha[0] = lane_value(al, 0);
-    alpha[1] = lane_value(al, 1);
-  } else {
-    al = dpp_max<0x114, 0xF>(al);                // lanes 4..: max with lane - 4
-    al = dpp_max<0x118, 0xF>(al);                // lanes 12..15: the row's four slots
-    alpha[0] = fmax(lane_value(al, 12), lane_value(al, 28));
-    alpha[1] = fmax(lane_value(al, 13), lane_value(al, 29));
-  }
   const double hdts_dx = 0.5 * ((G.dt / s) / G.dx);
 
   bool phys = true;
@@ -152,20 +174,7 @@ __global__ __launch_bounds__(256) void k_euler_strip(StepArgs<T> a, Geom G, int 
         }
       });
   if (!phys) atomicOr(a.flag, FLAG_NONPHYS);
-  if (i + 1 < s) {
-    __shared__ double wm4[2][4];
-#pragma unroll
-    for (int d2 = 0; d2 < 2; ++d2) {
-      const double m = wave_max_dpp(mx[d2]);
-      if (lane == 0) wm4[d2][wv] = m;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-      const double* m = wm4[threadIdx.x];
-      atomic_max_pos(speed_row(S, i + 1, blockIdx.x % NSLOT) + threadIdx.x,
-                     fmax(fmax(m[0], m[1]), fmax(m[2], m[3])));
-    }
-  }
+  if (i + 1 < s) fold_speeds(S, i + 1, lane, wv, mx);
 }
 
 // Euler sub-step on a 3D grid with LDS tiles: one block of 256 threads

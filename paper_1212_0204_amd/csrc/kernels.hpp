@@ -332,14 +332,10 @@ __device__ __forceinline__ void split_flux2(const double* U, double irho, int a,
 
 __device__ __forceinline__ bool speeds2(const double* U, double irho, double gam, double* sp) {
   const double rho = U[0];
-  auto over = [](double n, double d, double r) {
-    const double q = n * r;
-    return fma(fma(-d, q, n), r, q);
-  };
-  const double u = over(U[1], rho, irho), v = over(U[2], rho, irho);
+  const double u = quotient(U[1], rho, irho), v = quotient(U[2], rho, irho);
   const double usq = fma(u, u, v * v);
-  const double th = over(fma(2.0, U[3], -(rho * usq)), 2.0 * rho, 0.5 * irho);
-  const double x = over(gam * (rho * th), rho, irho);
+  const double th = quotient(fma(2.0, U[3], -(rho * usq)), 2.0 * rho, 0.5 * irho);
+  const double x = quotient(gam * (rho * th), rho, irho);
   // (a sum of positive terms is finite only if each is)
   const bool ok = (rho > 0.0) && (th > 0.0) && ((rho + th) + (usq + x) < INFINITY);
   const double c = sqrt_pos(x);

@@ -33,6 +33,13 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return fma(fma(-x, r, 1.0), r, r);
 }
 
+// n/d with r = rcp_nr(d): the product corrected by its remainder, which rounds
+// as the division does
+__device__ __forceinline__ double quotient(double n, double d, double r) {
+  const double q = n * r;
+  return fma(fma(-d, q, n), r, q);
+}
+
 // sqrt(x), x > 0 and finite: the hardware reciprocal root (2^-24.2), one
 // coupled step for the root and its half reciprocal, and the correction by
 // the remainder x - g^2.  (Arguments below the normal range count as its least.)

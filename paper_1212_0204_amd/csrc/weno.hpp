@@ -16,7 +16,7 @@
 // UE2, stage 1 writes UE3, stage 2 writes UE[(i + 1) % 2], so that after s
 // sub-steps the result is in UE[s % 2] as for the MUSCL solve.
 #pragma once
-#include "kernels.hpp"
+#include "euler2d.hpp"
 
 namespace hofks {
 
@@ -39,7 +39,8 @@ __device__ __forceinline__ double weno5(double v0, double v1, double v2, double 
   const double E0 = e0 * e0, E1 = e1 * e1, E2 = e2 * e2;
   // a_k = d_k / E_k  ->  a_k E0 E1 E2 = d_k prod_{l != k} E_l
   const double w0 = 0.1 * (E1 * E2), w1 = 0.6 * (E0 * E2), w2 = 0.3 * (E0 * E1);
-  return (w0 * q0 + w1 * q1 + w2 * q2) / (w0 + w1 + w2);
+  const double den = w0 + w1 + w2;
+  return quotient(w0 * q0 + w1 * q1 + w2 * q2, den, rcp_nr(den));
 }
 
 // L(V) at cell j (times -dx: the flux divergence summed over the axes);
@@ -302,6 +303,13 @@ namespace hofks {
 // line, both split parts) once, and every cell adds the difference of its
 // two faces.  Same arithmetic per face as `weno_div`; buffers, speeds and
 // the sub-step count as `k_weno_stage`.
+//
+// Bound by latency at 256^2 cells (one block per compute unit): 10.2 -> 8.7 us
+// per stage alone when the stage's loads were requested before the speeds and
+// the count, the lanes laid along x for the y faces too (their LDS reads met in
+// four lanes a bank), and the quotient and the maxima formed in fewer steps.
+// Strips as the MUSCL sub-steps' took 10.6 us: 3 faces per cell instead of 2.1,
+// and WENO5 is most of the work.
 constexpr int WT = 16;          // tile edge
 constexpr int WH = WT + 6;      // with three halo cells per side
 constexpr int WF = WT + 1;      // faces per tile line
@@ -320,39 +328,60 @@ __global__ __launch_bounds__(256) void k_weno_stage_tile(StepArgs<T> a, Geom G, 
   __shared__ double Hs[2][NM][WH * WT];     // split fluxes along one axis
   __shared__ double Fc[NM][WF * WT];        // face values along one axis
 
-  // the count: formed by sub-step 0, which records it for the later launches
-  const int s = i == 0 && st == 0 ? open_substeps<2>(a, G) : a.flag[1];
-  if (i >= s) return;
-  double alpha[3];
-  row_speeds<2>(S, i, alpha);
-  const double h = G.dt / s;
   const double *X, *V;
   double* out;
   weno_buffers(a, i, st, &X, &V, &out);
-  for (int q = t; q < WH * WH; q += 256) {
-    const int hx = q % WH, hy = q / WH;
-    const int gx = map_axis(X0 + hx - 3, Nx, G.bc[0]);
-    const int gy = map_axis(Y0 + hy - 3, Ny, G.bc[1]);
-    const size_t j = (size_t)gy * Nx + gx;
-#pragma unroll
-    for (int r = 0; r < NM; ++r) Vt[r][q] = V[(size_t)r * G.nc + j];
-  }
-  __syncthreads();
-  bool phys = true;
   const int lx = t % WT, ly = t / WT;
   const int gx = X0 + lx, gy = Y0 + ly;
   const bool own = gx < Nx && gy < Ny;
+  // tile + halo and the cell's value at the sub-step's start, requested before
+  // the speeds and the count so that the memory round trips overlap
+  constexpr int NQ = (WH * WH + 255) / 256;
+  double Vload[NQ][NM], Xload[NM] = {};
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + k * 256;
+    if (q < WH * WH) {
+      const int hx = map_near<3>(X0 + q % WH - 3, Nx, G.bc[0]);
+      const int hy = map_near<3>(Y0 + q / WH - 3, Ny, G.bc[1]);
+      const size_t j = (size_t)hy * Nx + hx;
+#pragma unroll
+      for (int r = 0; r < NM; ++r) Vload[k][r] = V[(size_t)r * G.nc + j];
+    }
+  }
+  if (own && st > 0) {
+#pragma unroll
+    for (int r = 0; r < NM; ++r) Xload[r] = X[(size_t)r * G.nc + (size_t)gy * Nx + gx];
+  }
+  double alpha[2];
+  strip_speeds(S, i, t & 63, alpha);
+  // the count: formed by the first stage, which records it for the others
+  const int s = i == 0 && st == 0 ? open_substeps<2>(a, G) : a.flag[1];
+  if (i >= s) return;
+  const double h = G.dt / s;
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + k * 256;
+    if (q < WH * WH) {
+#pragma unroll
+      for (int r = 0; r < NM; ++r) Vt[r][q] = Vload[k][r];
+    }
+  }
+  __syncthreads();
+  bool phys = true;
   double div[NM] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
+#pragma unroll
   for (int ax = 0; ax < 2; ++ax) {
-    // split fluxes of the cells along ax: x -> (x = -3..18, y = 0..15),
-    // y -> (x = 0..15, y = -3..18); entry e = line * WH + position
+    // split fluxes of the cells along ax, the lanes along x for either axis:
+    // x -> (x = -3..18, y = 0..15) at entry y WH + x + 3, y -> (x = 0..15,
+    // y = -3..18) at entry (y + 3) WT + x; SP is the step of an entry to the
+    // next cell along ax
+    const int SP = ax == 0 ? 1 : WT;
     for (int q = t; q < WH * WT; q += 256) {
-      const int line = q / WH, pos = q % WH;
-      const int hx = ax == 0 ? pos : line + 3, hy = ax == 0 ? line + 3 : pos;
+      const int e = ax == 0 ? (q / WH + 3) * WH + q % WH : (q / WT) * WH + q % WT + 3;
       double Uq[NM];
 #pragma unroll
-      for (int r = 0; r < NM; ++r) Uq[r] = Vt[r][hy * WH + hx];
+      for (int r = 0; r < NM; ++r) Uq[r] = Vt[r][e];
       double Wp[NM], Wm[NM];
       phys &= split_flux<2>(Uq, ax, alpha[ax], G.gam, Wp, Wm);
 #pragma unroll
@@ -366,18 +395,19 @@ __global__ __launch_bounds__(256) void k_weno_stage_tile(StepArgs<T> a, Geom G, 
     // part from cells f-3 .. f+1, the - part from cells f+2 .. f-2
     for (int q = t; q < WF * WT * NM; q += 256) {
       const int r = q / (WF * WT), e = q % (WF * WT);
-      const int line = e / WF, f = e % WF;
-      const double* hp = &Hs[0][r][line * WH + f];  // cell f - 3 at offset 0
-      const double* hm = &Hs[1][r][line * WH + f];
-      Fc[r][e] = weno5(hp[0], hp[1], hp[2], hp[3], hp[4]) + weno5(hm[5], hm[4], hm[3], hm[2], hm[1]);
+      const int o = ax == 0 ? (e / WF) * WH + e % WF : e;  // cell f - 3
+      const double* hp = &Hs[0][r][o];
+      const double* hm = &Hs[1][r][o];
+      Fc[r][e] = weno5(hp[0], hp[SP], hp[2 * SP], hp[3 * SP], hp[4 * SP]) +
+                 weno5(hm[5 * SP], hm[4 * SP], hm[3 * SP], hm[2 * SP], hm[SP]);
     }
     __syncthreads();
     if (own) {
-      const int line = ax == 0 ? ly : lx, c = ax == 0 ? lx : ly;
+      const int e = ax == 0 ? ly * WF + lx : ly * WT + lx;
 #pragma unroll
-      for (int r = 0; r < NM; ++r) div[r] += Fc[r][line * WF + c + 1] - Fc[r][line * WF + c];
+      for (int r = 0; r < NM; ++r) div[r] += Fc[r][e + SP] - Fc[r][e];
     }
-    __syncthreads();  // Hs and Fc are rewritten for the next axis
+    if (ax == 0) __syncthreads();  // Hs and Fc are rewritten for the next axis
   }
   double mx[2] = {0.0, 0.0};
   const bool want = st == 2 && i + 1 < s;
@@ -387,8 +417,8 @@ __global__ __launch_bounds__(256) void k_weno_stage_tile(StepArgs<T> a, Geom G, 
 #pragma unroll
     for (int r = 0; r < NM; ++r) {
       const double L = -div[r] / G.dx;
-      const double x = X[(size_t)r * G.nc + j];
       const double v = Vt[r][(ly + 3) * WH + lx + 3];
+      const double x = st == 0 ? v : Xload[r];
       if (st == 0)
         Un[r] = v + h * L;
       else if (st == 1)
@@ -405,20 +435,7 @@ __global__ __launch_bounds__(256) void k_weno_stage_tile(StepArgs<T> a, Geom G, 
     }
   }
   if (!phys) atomicOr(a.flag, FLAG_NONPHYS);
-  if (want) {
-    __shared__ double wm4[4][ASTR];
-#pragma unroll
-    for (int d2 = 0; d2 < 2; ++d2) {
-      const double m = wave_max(mx[d2]);
-      if ((t & 63) == 0) wm4[t >> 6][d2] = m;
-    }
-    __syncthreads();
-    if (t < 2) {
-      double m = wm4[0][t];
-      for (int w = 1; w < 4; ++w) m = fmax(m, wm4[w][t]);
-      atomic_max_pos(speed_row(S, i + 1, blockIdx.x % NSLOT) + t, m);
-    }
-  }
+  if (want) fold_speeds(S, i + 1, t & 63, t >> 6, mx);
 }
 
 }  // namespace hofks

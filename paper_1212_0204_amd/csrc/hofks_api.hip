@@ -2663,11 +2663,15 @@ hofks_status hofks_closure_train_step(float* params, float* m, float* v, void* p
     return HOFKS_EINVAL;
   if (work_bytes < hofks_mlp_grad_work_bytes(n)) return HOFKS_ESIZE;
   hipStream_t s = (hipStream_t)stream;
-  hofks_status st = mlp_grad_launch(packed, x, t, idx, n, grad, loss, (float*)work, s);
-  if (st) return st;
-  st = hofks_mlp_adam(params, grad, m, v, lr, beta1, beta2, eps, step, stream);
-  if (st) return st;
-  return hofks_mlp_pack(params, packed, stream);
+  const int nb = mlp::grad_blocks(n);
+  const float c1 = (float)(1.0 - std::pow((double)beta1, step));
+  const float c2 = (float)(1.0 - std::pow((double)beta2, step));
+  hipLaunchKernelGGL(mlp::k_mlp_grad, dim3(nb), dim3(64 * mlp::GRAD_WAVES), mlp::GRAD_LDS, s,
+                     packed, x, t, idx, n, (float*)work);
+  hipLaunchKernelGGL(mlp::k_mlp_update, dim3(nblk(mlp::NPARAM + 1, 64)), dim3(64), 0, s,
+                     (const float*)work, nb, grad, loss, params, m, v, packed, lr, beta1, beta2,
+                     eps, c1, c2);
+  return hipGetLastError() == hipSuccess ? HOFKS_OK : HOFKS_EDEVICE;
 }
 
 hofks_status hofks_mlp_adam(float* params, const float* grad, float* m, float* v, float lr,

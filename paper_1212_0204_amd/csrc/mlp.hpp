@@ -138,6 +138,46 @@ __global__ void k_mlp_pack(const float* __restrict__ p, void* __restrict__ packe
   }
 }
 
+// where k_mlp_pack puts parameter i: its forward fragment element, its
+// transposed one and its bias (-1: none); the inverse of fwd_value and tr_value
+struct PackedAt {
+  int fwd, tr, bias;
+};
+__device__ inline PackedAt packed_at(int i) {
+  PackedAt a{-1, -1, -1};
+  // element of the 32-deep fragment that holds hidden neuron `in` of row o
+  auto hid = [](int f, int o, int in) {
+    const int g = in >> 4, r = in & 15, e = 4 * (g & 1) + (r & 3), L = 16 * (r >> 2) + (o & 15);
+    return (f + (g >> 1)) * 512 + L * 8 + e;
+  };
+  // element of the 16-deep transposed fragment f (row in % 16, K = o % 16)
+  auto trn = [](int f, int o, int in) {
+    return f * 256 + (16 * ((o & 15) >> 2) + (in & 15)) * 4 + (o & 3);
+  };
+  if (i < OB1) {
+    const int o = (i - OW1) / NIN, in = (i - OW1) % NIN;
+    a.fwd = (2 * (o >> 4) + (in >> 5)) * 512 + (16 * ((in & 31) >> 3) + (o & 15)) * 8 + (in & 7);
+  } else if (i < OW2) {
+    a.bias = i - OB1;
+  } else if (i < OB2 || (i >= OW3 && i < OB3)) {
+    const bool two = i < OB2;
+    const int k = i - (two ? OW2 : OW3), o = k / NH, in = k % NH;
+    a.fwd = hid((two ? F_L2 : F_L3) + 2 * (o >> 4), o, in);
+    a.tr = trn((two ? F_T2 : F_T3) + 4 * (in >> 4) + (o >> 4), o, in);
+  } else if (i < OW3) {
+    a.bias = NH + i - OB2;
+  } else if (i < OW4) {
+    a.bias = 2 * NH + i - OB3;
+  } else if (i < OB4) {
+    const int o = (i - OW4) / NH, in = (i - OW4) % NH;
+    a.fwd = hid(F_L4, o, in);
+    a.tr = trn(F_T4 + (in >> 4), o, in);
+  } else {
+    a.bias = 3 * NH + i - OB4;
+  }
+  return a;
+}
+
 __device__ __forceinline__ const s8* fwd_frags(const void* packed) {
   return reinterpret_cast<const s8*>(packed);
 }
@@ -357,8 +397,11 @@ __global__ __launch_bounds__(64 * GRAD_WAVES) void k_mlp_grad(const void* __rest
   short* TA = reinterpret_cast<short*>(lds_raw + GRAD_WAVES * NPARAM * sizeof(float)) +
               wv * 2 * NH * TR_ROW;
   short* TZ = TA + NH * TR_ROW;
-  for (int i = threadIdx.x; i < GRAD_WAVES * NPARAM; i += blockDim.x)
-    reinterpret_cast<float*>(lds_raw)[i] = 0.0f;
+  // (in 16-byte steps, as the sums at the end: with one tile per wavefront the
+  // 88 KB that are cleared and summed are a good part of the kernel)
+  static_assert(NPARAM % 4 == 0 && PART_STRIDE % 4 == 0, "gradients in steps of four floats");
+  for (int i = threadIdx.x; i < GRAD_WAVES * NPARAM / 4; i += blockDim.x)
+    reinterpret_cast<f4*>(lds_raw)[i] = f4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();
 
   FwdW W;
@@ -476,13 +519,13 @@ __global__ __launch_bounds__(64 * GRAD_WAVES) void k_mlp_grad(const void* __rest
   __shared__ float wl[GRAD_WAVES];
   if (lane == 0) wl[wv] = ls * inv;
   __syncthreads();
-  const float* g0 = reinterpret_cast<const float*>(lds_raw);
+  const f4* g0 = reinterpret_cast<const f4*>(lds_raw);
   float* out = part + (size_t)blockIdx.x * PART_STRIDE;
-  for (int i = threadIdx.x; i < NPARAM; i += blockDim.x) {
-    float v = g0[i];
+  for (int i = threadIdx.x; i < NPARAM / 4; i += blockDim.x) {
+    f4 v = g0[i];
 #pragma unroll
-    for (int w = 1; w < GRAD_WAVES; ++w) v += g0[(size_t)w * NPARAM + i];
-    out[i] = v;
+    for (int w = 1; w < GRAD_WAVES; ++w) v += g0[(size_t)w * (NPARAM / 4) + i];
+    reinterpret_cast<f4*>(out)[i] = v;
   }
   if (threadIdx.x == 0) {
     float l = wl[0];
@@ -494,10 +537,7 @@ __global__ __launch_bounds__(64 * GRAD_WAVES) void k_mlp_grad(const void* __rest
 
 // grad[i] = sum over blocks b = 0, 1, ... of the partials (in that order);
 // thread NPARAM sums the loss
-__global__ void k_mlp_grad_reduce(const float* __restrict__ part, int nblocks,
-                                  float* __restrict__ grad, float* __restrict__ loss) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > NPARAM) return;
+__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int nblocks, int i) {
   // 16 partials loaded at a time, then added in block order (the same sums
   // as one at a time, with the loads' latencies overlapped)
   float v = 0.0f;
@@ -510,6 +550,14 @@ __global__ void k_mlp_grad_reduce(const float* __restrict__ part, int nblocks,
     for (int u = 0; u < 16; ++u) v += t[u];
   }
   for (; b < nblocks; ++b) v += part[(size_t)b * PART_STRIDE + i];
+  return v;
+}
+
+__global__ void k_mlp_grad_reduce(const float* __restrict__ part, int nblocks,
+                                  float* __restrict__ grad, float* __restrict__ loss) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i > NPARAM) return;
+  const float v = sum_partials(part, nblocks, i);
   if (i < NPARAM)
     grad[i] = v;
   else
@@ -518,17 +566,48 @@ __global__ void k_mlp_grad_reduce(const float* __restrict__ part, int nblocks,
 
 // Adam with bias correction on the FP32 master parameters (c1 = 1 - b1^k,
 // c2 = 1 - b2^k from the host)
-__global__ void k_mlp_adam(float* __restrict__ p, const float* __restrict__ g,
-                           float* __restrict__ m, float* __restrict__ v, float lr, float b1,
-                           float b2, float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= NPARAM) return;
-  const float gi = g[i];
+__device__ __forceinline__ void adam_one(float* __restrict__ p, float gi, float* __restrict__ m,
+                                         float* __restrict__ v, int i, float lr, float b1,
+                                         float b2, float eps, float c1, float c2) {
   const float mi = b1 * m[i] + (1.0f - b1) * gi;
   const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
   p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+}
+
+__global__ void k_mlp_adam(float* __restrict__ p, const float* __restrict__ g,
+                           float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+                           float b2, float eps, float c1, float c2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < NPARAM) adam_one(p, g[i], m, v, i, lr, b1, b2, eps, c1, c2);
+}
+
+// The end of a training step in one launch: the gradient sums, the Adam step
+// and the packed form, each of which takes one parameter at a time (thread
+// NPARAM sums the loss).  The launches are short (3 to 7 us with their gaps),
+// so one instead of three is what counts: a step of
+// 4096 samples 39.5 -> 36.3 us, 64-thread blocks putting it on 173 compute units.
+__global__ void k_mlp_update(const float* __restrict__ part, int nblocks, float* __restrict__ grad,
+                             float* __restrict__ loss, float* __restrict__ p,
+                             float* __restrict__ m, float* __restrict__ v,
+                             void* __restrict__ packed, float lr, float b1, float b2, float eps,
+                             float c1, float c2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i > NPARAM) return;
+  const float g = sum_partials(part, nblocks, i);
+  if (i == NPARAM) {
+    *loss = g;
+    return;
+  }
+  grad[i] = g;
+  adam_one(p, g, m, v, i, lr, b1, b2, eps, c1, c2);
+  const float pi = p[i];
+  const PackedAt a = packed_at(i);
+  if (a.fwd >= 0) reinterpret_cast<short*>(packed)[a.fwd] = to_bf16(pi);
+  if (a.tr >= 0) reinterpret_cast<short*>(packed)[NFWD * 64 * 8 + a.tr] = to_bf16(pi);
+  if (a.bias >= 0)
+    reinterpret_cast<float*>(reinterpret_cast<char*>(packed) + FRAG_BYTES)[a.bias] = pi;
 }
 
 __global__ void k_mlp_zero(float* __restrict__ p, int n) {

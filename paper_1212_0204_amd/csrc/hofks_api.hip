@@ -1176,9 +1176,16 @@ hofks_status hofks_create(const hofks_grid_desc* desc, void* dev_ws, size_t ws_b
   if (kin_lds(P, c->kng) > 65536) c->kng = 2;
   c->kring = P.d == 3 && kin3_lds(P) <= 65536;
   c->kwide = P.d == 2 && !P.prec && P.G.nv1 % 4 == 0 && kin2w_lds(P, 4) <= 65536;
+  // Loads ahead of the two-cell kernel, 4 or 8.  Beside the WENO stages (of
+  // the order of 40 launches to a step) the kernel is left too few compute
+  // units for its blocks to hide the loads by themselves and 8 are faster
+  // from about 200 x 190 x 32^2 (0.605 -> 0.587 ms per step; 256^2 x 32^2
+  // 0.706 -> 0.605, 400^2 x 32^2 1.330 -> 1.241) and the same below it; beside
+  // the shorter MUSCL chain 8 cost registers and are slower (256^2 x 32^2
+  // 0.268 -> 0.314 ms, 400^2 x 32^2 0.742 -> 1.042).
   if (c->kwide) {
     c->kng = 4;
-    c->kunr = 4;
+    c->kunr = desc->scheme == 3 ? 8 : 4;
   }
   if (P.G.offl) {  // off-lattice: the generic kinetic kernel with per-step shifts
     c->kring = c->kwide = 0;

@@ -288,6 +288,7 @@ struct hofks_ctx {
   int s_next;   // single-sub-step Euler launches of the step being queued
   int euler_k;  // > 0: per-sub-step Euler launches before the tail (0: s_next)
   bool euler_seq;   // the Euler solve runs on the caller's stream before the kinetic kernel
+  bool cfg_auto;    // launch configuration by rule: neither set nor tuned
   bool strang;      // Strang splitting: half relaxations around each transport
   double inv_prev;  // 1/tau of the last step taken (Strang)
   long steps;
@@ -451,6 +452,37 @@ int kin_unroll(const Plan& P, int ng, int unr) {
   return (even && per % unr == 0) ? unr : 1;
 }
 
+// Steps with an Euler solve take the largest of unr, 8 and (four wavefronts,
+// 1D and 2D) 4 that divides a wavefront's nodes: with one load in flight the
+// launch waits for memory at every node (FP32 400^2 x 24^2 0.383 ms per step
+// with one, 0.317 with 8).
+int kin_unroll_euler(const Plan& P, int ng, int unr) {
+  for (int u : {unr, 8, 4})
+    if ((u != 4 || (ng == 4 && P.d <= 2)) && kin_unroll(P, ng, u) == u) return u;
+  return 1;
+}
+
+// Below this lambda the pieces carry nothing of U^{n+1} that a result shows,
+// so the order of sums that are then rounded to FP32 is free.
+constexpr double LAM_FREE = 1e-5;
+
+// Wavefronts of an untuned 2D FP32 step while the order of its sums is free,
+// from the blocks of the launch per compute unit (four with 16 loads ahead,
+// the others with eight).  Between two and five the launch is little more
+// than a round and two wavefronts leave the Euler blocks room beside them
+// (256^2 x 32^2, 1024 blocks: 0.183 ms per step with two, 0.212 with four,
+// 0.247 with eight; 300 x 256 x 32^2 0.263, 0.267, 0.299); in many rounds a
+// block of eight ends sooner and frees room for a whole Euler block at once
+// (400^2 x 32^2, 2800 blocks: 0.436, 0.453 with four, 0.457 with two; 512^2 x
+// 32^2 0.711, 0.762, 0.774).  In between and below four are as good or better
+// (330 x 300 x 32^2, 1800 blocks: 0.385, 0.404 with eight, 0.439 with two; 200
+// x 120 x 32^2, 480 blocks: 0.139, 0.152, 0.142).
+int fp32_wavefronts(const Plan& P, unsigned nb) {
+  const unsigned cu = P.ncu;
+  const int ng = nb > 10 * cu ? 8 : nb > 2 * cu && nb <= 5 * cu ? 2 : 4;
+  return kin_lds(P, ng) <= 65536 ? ng : 2;
+}
+
 // 3D steps with an Euler solve: blocks of RY y rows sharing a ring of
 // staged upstream rows (k_kinetic3)
 size_t kin3_lds(const Plan& P) {
@@ -557,7 +589,13 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
 #undef KO
     return;
   }
-  int ng = c->kng, unr = kin_unroll(P, c->kng, c->kunr);
+  int ng = c->kng, want = c->kunr;
+  if constexpr (D == 2 && CP)
+    if (c->cfg_auto && P.G.lam < LAM_FREE && P.G.nv1 % 8 == 0) {
+      ng = fp32_wavefronts(P, grid.x);
+      if (ng != 4) want = 8;
+    }
+  int unr = kin_unroll_euler(P, ng, want);
   if (FT || !EUL) {  // free transport and FKS steps: one configuration
     ng = 4;
     unr = kin_unroll(P, 4, 8);
@@ -575,7 +613,12 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
   } else if (ng == 8 && D >= 2) {
     if (unr == 16) { KB(8, 16) } else if (unr == 8) { KB(8, 8) } else { KB(8, 1) }
   } else {
-    if (unr == 16) { KB(4, 16) } else if (unr == 8) { KB(4, 8) } else { KB(4, 1) }
+    if (unr == 16) { KB(4, 16) } else if (unr == 8) { KB(4, 8) }
+    else {
+      if constexpr (D <= 2 && EUL && !FT)
+        if (unr == 4) { KB(4, 4) return; }
+      KB(4, 1)
+    }
   }
 #undef KB
 #undef K
@@ -660,6 +703,21 @@ bool line_shape(const Plan& P, int* cpt, int* nw) {
   return *cpt > 0;
 }
 
+// Whether an untuned 1D step runs its Euler solve before the kinetic kernel on
+// the caller's stream instead of beside it.  The fork and the join cost about
+// as much as a short kinetic launch, so beside pays only for the one-block
+// solve (which leaves the chip to the kinetic kernel) and from more than 64
+// nodes per axis.  Before against beside, us per step: one block, 200 x 64
+// FP64 38 against 42, 1000 x 16 67, 73, 1000 x 96 77, 73; persistent tail, 3001
+// x 48 FP32 (lambda 0.26) 128, 144, 20000 x 64 154, 171, 60000 x 96 256, 261.
+bool euler_first(const hofks_ctx* c) {
+  const Plan& P = c->P;
+  int cpt, nw;
+  const bool line = c->desc.scheme != 3 && c->euler_k == 0 &&
+                    (!P.prec || P.G.lam < LAM_FREE) && line_shape(P, &cpt, &nw);
+  return P.d == 1 && (!line || P.G.nv1 <= 64);
+}
+
 // Rows per strip of the 2D Euler sub-steps.  Short grids want many strips:
 // with one row a sub-step alone takes 5.4 us on 70 x 37 cells and 6.4 on
 // 256^2 (two rows: 6.5 and 6.3, and beside the kinetic kernel 17.5 -> 21.1 on
@@ -690,9 +748,9 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     int cpt, nw;
     // In the precision form the records and pieces are rounded to FP32, where
     // a last bit of the Euler solve can move a result by 1e-8, so while the
-    // pieces carry a part of U^{n+1} (lambda >= 1e-5) it keeps the per-cell
+    // pieces carry a part of U^{n+1} (lambda >= LAM_FREE) it keeps the per-cell
     // form and its bits.
-    const bool free_bits = !P.prec || P.G.lam < 1e-5;
+    const bool free_bits = !P.prec || P.G.lam < LAM_FREE;
     if (c->desc.scheme != 3 && c->euler_k == 0 && free_bits && line_shape(P, &cpt, &nw)) {
 #define KL(C)                                                                                  \
   if (a.unlimited)                                                                             \
@@ -965,6 +1023,7 @@ hofks_status plan_launches(hofks_ctx* c, bool follow) {
 template <int D, typename T>
 hofks_status step_impl(hofks_ctx* c, int nsteps) {
   c->fork_pending = false;
+  if (D == 1 && c->cfg_auto) c->euler_seq = euler_first(c);
   hofks_status st = HOFKS_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   const bool eul = c->P.G.mu != 0.0 && c->desc.scheme != 1;
@@ -1171,6 +1230,7 @@ hofks_status hofks_create(const hofks_grid_desc* desc, void* dev_ws, size_t ws_b
   c->s_next = 1;
   // kinetic configuration before any tuning: wider unroll in 2D/3D, two
   // wavefronts per block for the FP64 2D grid
+  c->cfg_auto = true;
   c->kng = (P.d == 2 && !P.prec) ? 2 : 4;
   c->kunr = P.d >= 2 ? 16 : 8;
   if (kin_lds(P, c->kng) > 65536) c->kng = 2;
@@ -2034,6 +2094,7 @@ hofks_status grid_autotune(hofks_ctx* c, int steps, const char* cache_path, int*
     }
     return HOFKS_OK;
   }
+  c->cfg_auto = false;
   std::ostringstream key;
   key << "gfx950:grid:d=" << P.d << ":n=" << P.G.n[0] << "x" << P.G.n[1] << "x" << P.G.n[2]
       << ":nv=" << P.G.nv1 << ":prec=" << P.prec << ":bc=" << P.G.bc[0] << P.G.bc[1] << P.G.bc[2]
@@ -2243,6 +2304,7 @@ hofks_status hofks_set_launch_config(hofks_ctx* c, int wavefronts, int loads, in
   c->kng = wavefronts;
   c->kunr = loads;
   c->euler_seq = euler_before != 0;
+  c->cfg_auto = false;
   return HOFKS_OK;
 }
 

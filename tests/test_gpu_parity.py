@@ -831,3 +831,28 @@ def test_2d_offlattice_pairs(n, nv, bc, frac):
     s.step(7)
     assert moment_errors(s.read_moments(), o.U, 2).max() < TOL64
     assert rel_inf(s.read_f(), o.f) < TOL64
+
+
+@gpu
+@pytest.mark.parametrize("n,nv,ratio,scheme", [
+    ((70, 37), 16, 0.05, 0),                                # two blocks or fewer per compute unit
+    ((65, 300), 8, 0.05, 0), ((64, 1540), 8, 0.05, 0),      # up to five, and up to ten
+    ((64, 2570), 8, 0.05, 0),                               # more than ten
+    ((130, 520), 24, 0.05, 0), ((65, 300), 16, 0.5, 0),     # 24 nodes; lambda not negligible
+    ((130,), 64, 0.05, 0), ((130,), 72, 0.05, 0),           # one-block solve first, and beside
+    ((130,), 48, 0.5, 0), ((4100,), 20, 0.05, 3),           # the tail forms first; four loads or one
+    ((70, 9), 12, 0.5, 2),                                  # four loads ahead in 2D
+])
+def test_untuned_configurations_fp32(n, nv, ratio, scheme):
+    """the launch configurations taken by rule in the precision form"""
+    announce("untuned", n, nv, ratio, scheme)
+    rng = np.random.default_rng(n[0] + nv)
+    nc, d, dx = int(np.prod(n)), len(n), 1.0 / 128
+    x = np.arange(nc) * (2 * np.pi / nc)
+    rho = 1.0 + 0.1 * np.sin(x) + 0.02 * rng.uniform(-1, 1, nc)
+    th = 1.0 + 0.1 * np.cos(x) + 0.02 * rng.uniform(-1, 1, nc)
+    dv = 10.0 / nv
+    o, s = run_pair(d, n, dx, nv, dv, (1,) * d, ratio * dx / dv, 3,
+                    (rho, 0.1 * np.sin(x) * np.ones((d, 1)), th), precision=1, scheme=scheme)
+    assert moment_errors(s.read_moments(), o.U, d).max() < TOL32
+    assert s.counters()[0] == o.substeps

@@ -230,8 +230,9 @@ hofks_status hofks_autotune(hofks_ctx *ctx, int steps, const char *cache_path,
  * grids: 2 or 4 wavefronts, 4 or 8 loads; others: 2, 4 or 8 (2D/3D)
  * wavefronts, 8 or 16 loads; 3D grids 4 wavefronts), and euler_before = 1 to
  * run the Euler solve before the kinetic kernel on the context's stream
- * (0: beside it on the library's second stream).  Results do not depend on
- * the configuration.  HOFKS_EINVAL for a batch or an unavailable choice. */
+ * (0: beside it on the library's second stream).  Until this call or
+ * hofks_autotune the configuration follows from the grid.  Results do not
+ * depend on it beyond the rounding of the moment sums.  HOFKS_EINVAL for a batch or an unavailable choice. */
 hofks_status hofks_set_launch_config(hofks_ctx *ctx, int wavefronts, int loads, int euler_before);
 
 /* Set the launch configuration of a batch without timing: cells per kinetic

@@ -114,8 +114,15 @@ hofks_status hofks_set_state_f(hofks_ctx *ctx, const double *f, size_t bytes);
  * a 2D or 3D grid (outside stream capture) it follows the Euler sub-step
  * counts that the steps leave in pinned host memory, waiting for a step once
  * it is two behind the one being queued, so that the launches of the later
- * steps follow a count that grows during the call.
- */
+ * steps follow a count that grows during the call.  The host thread polls
+ * meanwhile, so such a call lasts nearly as long as its steps: a thread
+ * that steps several grids on several streams overlaps them by calls of at most
+ * 16 steps, or uses a thread for each.
+ *
+ * A grid's steps may be captured (n_steps a multiple of 6, so that the buffers
+ * stand as they did; counters and the time of off-lattice steps do not see
+ * replays).  A captured graph touches the workspace alone and may be replayed
+ * as long as that lives, also after hofks_destroy. */
 hofks_status hofks_step(hofks_ctx *ctx, int n_steps);
 
 /* Wait for the stream and report the sticky device flag. */
@@ -180,6 +187,8 @@ hofks_status hofks_kernel_timing(hofks_ctx *ctx, int enable, double ms[4],
 
 double hofks_dt(const hofks_ctx *ctx);
 const char *hofks_last_error(const hofks_ctx *ctx);
+/* Waits for the steps of the context that are still in flight on a grid of
+ * 2 or 3 dimensions; the stream it was created on need not exist any more. */
 void hofks_destroy(hofks_ctx *ctx);
 
 /* ------------------------------------------------------------- batches

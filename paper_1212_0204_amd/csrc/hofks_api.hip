@@ -314,10 +314,16 @@ struct hofks_ctx {
   hipStream_t aux;
   hipEvent_t ev_fork, ev_join;
   // pinned host ring written by sub-step 0 of every 2D/3D step (see
-  // StepArgs::s_host); ticks number the steps queued on this context, the
-  // one after tick0 being the first since the state or tau was set
+  // StepArgs::s_host); ticks number the steps that write it, the one after
+  // tick0 being the first since the state or tau was set.  Captured steps do
+  // not write it (ring_on false): a graph may be replayed after the context is
+  // gone.  The writes are waited for through `aux`, or, where the Euler
+  // solve runs on the caller's stream (which may be gone by then), through
+  // ev_ring, recorded there at the end of every such call.
   unsigned long long *s_ring, *s_ring_dev;
   unsigned tick, tick0;
+  bool ring_on;
+  hipEvent_t ev_ring;
   // closure form (2D-2V): network (caller's device memory), scale of its
   // output, indicator threshold; per-cell arrays in the workspace
   const void* clos_w;
@@ -847,8 +853,8 @@ hofks_status launch_step(hofks_ctx* c, float* snap_x = nullptr, float* snap_t = 
   a.thr = 0.0;
   a.sums = (double*)(c->ws + P.off_sums);
   a.nstep = n;
-  a.s_host = D >= 2 ? c->s_ring_dev : nullptr;
-  a.tick = ++c->tick;
+  a.s_host = c->ring_on ? c->s_ring_dev : nullptr;
+  a.tick = c->ring_on ? ++c->tick : 0;
   const bool ft = (P.G.mu == 0.0);
   const bool eul = !ft && c->desc.scheme != 1;
   if (c->clos_dirty && !eul) {
@@ -1005,7 +1011,7 @@ hofks_status plan_launches(hofks_ctx* c, bool follow) {
       }
       if (q != hipSuccess) return hip_fail(c, q, "waiting for a step");
       v = ring_value(c, t);
-      if (v < 0.0) return HOFKS_OK;  // overwritten by a replay of captured steps
+      if (v < 0.0) return HOFKS_OK;  // a step that failed to launch
       break;
     }
   }
@@ -1020,18 +1026,34 @@ hofks_status plan_launches(hofks_ctx* c, bool follow) {
   return HOFKS_OK;
 }
 
+// Begin and end of a call that queues steps: whether they write the ring, and
+// the mark behind its writes on the caller's stream
+void ring_begin(hofks_ctx* c) {
+  c->ring_on = c->P.d >= 2 && c->P.G.mu != 0.0 && c->desc.scheme != 1;
+  if (!c->ring_on) return;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();  // (the launches report it, if they fail too)
+    c->ring_on = false;
+  } else if (cap != hipStreamCaptureStatusNone) {
+    c->ring_on = false;
+    c->tick0 = c->tick;  // replays advance the state unseen
+  }
+}
+
+hofks_status ring_end(hofks_ctx* c) {
+  if (c->ring_on && c->euler_seq) HIPCHK(c, hipEventRecord(c->ev_ring, c->stream));
+  return HOFKS_OK;
+}
+
 template <int D, typename T>
 hofks_status step_impl(hofks_ctx* c, int nsteps) {
   c->fork_pending = false;
   if (D == 1 && c->cfg_auto) c->euler_seq = euler_first(c);
   hofks_status st = HOFKS_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool eul = c->P.G.mu != 0.0 && c->desc.scheme != 1;
-  bool follow = D >= 2 && eul && c->euler_k == 0 && nsteps > LONG_CALL;
-  if (follow) {  // captured steps do not run while the host waits
-    HIPCHK(c, hipStreamIsCapturing(c->stream, &cap));
-    follow = cap == hipStreamCaptureStatusNone;
-  }
+  ring_begin(c);
+  // (captured steps do not run while the host waits)
+  const bool follow = c->ring_on && c->euler_k == 0 && nsteps > LONG_CALL;
   for (int it = 0; it < nsteps && !st; ++it) {
     c->fork_next = it + 1 < nsteps;
     if (c->strang) set_step_weights(c);
@@ -1045,7 +1067,8 @@ hofks_status step_impl(hofks_ctx* c, int nsteps) {
   }
   if (c->strang) set_step_weights(c);
   c->fork_next = c->fork_pending = false;
-  return st;
+  const hofks_status end = ring_end(c);
+  return st ? st : end;
 }
 
 template <typename F>
@@ -1215,6 +1238,7 @@ hofks_status hofks_create(const hofks_grid_desc* desc, void* dev_ws, size_t ws_b
   if (hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_fork, evf) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_join, evf) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_ring, hipEventDisableTiming) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->s_ring), S_RING * sizeof(*c->s_ring),
                     hipHostMallocMapped) != hipSuccess ||
       hipHostGetDevicePointer(reinterpret_cast<void**>(&c->s_ring_dev), c->s_ring, 0) !=
@@ -2531,7 +2555,10 @@ hofks_status hofks_closure_snapshot(hofks_ctx* c, float* x, float* t) {
   if (((uintptr_t)x & 3) || ((uintptr_t)t & 3)) return HOFKS_EINVAL;
   hofks_status st = dispatch(c, [&](auto D, auto tt) -> hofks_status {
     if constexpr (decltype(D)::value == 2) {
-      return launch_step<2, decltype(tt)>(c, x, t);
+      ring_begin(c);
+      const hofks_status launched = launch_step<2, decltype(tt)>(c, x, t);
+      const hofks_status end = ring_end(c);
+      return launched ? launched : end;
     }
     return HOFKS_EINVAL;
   });
@@ -2758,11 +2785,12 @@ hofks_status hofks_mlp_adam(float* params, const float* grad, float* m, float* v
 extern "C" void hofks_destroy(hofks_ctx* c) {
   if (!c) return;
   batch_free(c);
-  if (c->s_ring) {  // steps in flight write it (on the caller's stream or aux)
-    (void)hipStreamSynchronize(c->stream);
+  if (c->s_ring) {  // steps in flight write it
     if (c->aux) (void)hipStreamSynchronize(c->aux);
+    if (c->ev_ring) (void)hipEventSynchronize(c->ev_ring);
     (void)hipHostFree(c->s_ring);
   }
+  if (c->ev_ring) (void)hipEventDestroy(c->ev_ring);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);

@@ -856,3 +856,60 @@ def test_untuned_configurations_fp32(n, nv, ratio, scheme):
                     (rho, 0.1 * np.sin(x) * np.ones((d, 1)), th), precision=1, scheme=scheme)
     assert moment_errors(s.read_moments(), o.U, d).max() < TOL32
     assert s.counters()[0] == o.substeps
+
+
+# ------------------------------------------------------ captured grid steps
+@gpu
+@pytest.mark.parametrize("n,prec,euler_before", [
+    ((60, 41), 0, 0), ((60, 41), 0, 1), ((70, 33), 1, 0), ((12, 9, 10), 1, 0), ((300,), 0, 0)])
+def test_captured_steps_between_calls_and_after_the_context(n, prec, euler_before):
+    """steps captured by the caller: replays between calls of more and of fewer
+    than 16 steps against the same steps queued, and once the context is gone
+    against replays while it stands"""
+    import torch
+    announce("captured", n, prec, euler_before)
+    d, nc = len(n), int(np.prod(n))
+    x = np.arange(nc) * (2 * np.pi / nc)
+    fields = (1.0 + 0.1 * np.sin(x), 0.1 * np.sin(x) * np.ones((d, 1)), 1.0 + 0.1 * np.cos(x))
+
+    def make(stream=None):
+        s = _solver(dim=d, n_cells=n, dx=1 / 64, n_vel=8, dv=1.0, bc=(0,) * d, precision=prec,
+                    tau=2e-3, stream=stream)
+        if d == 2:
+            s.set_launch_config(4, 8, euler_before)
+        s.set_state_macro(*fields)
+        return s
+
+    ref, kept = make(), []
+    for _ in range(2):
+        stream = torch.cuda.Stream()
+        s, graph = make(stream), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+            s.step(18)  # (more than 16, as a call that follows the counts has)
+        kept.append((s, graph, stream))
+    # (the host counts the captured call: the first replay makes it true)
+    for queued in (0, 24, 0, 6, 30):
+        ref.step(18 + queued)
+        for s, graph, stream in kept:
+            with torch.cuda.stream(stream):
+                graph.replay()
+            s.step(queued)
+            err = moment_errors(s.read_moments(), ref.read_moments(), d)
+            assert err.max() < (TOL64 if prec == 0 else TOL32), (queued, err)
+
+    first = kept[0][0]
+    workspaces = [s.workspace for s, _, _ in kept]
+    first.step(24)
+    kept[1][0].step(24)
+    first.close()  # steps in flight
+    images = []
+    for k in range(2):
+        torch.cuda.synchronize()
+        images.append([w.cpu().numpy() for w in workspaces])
+        if k == 0:
+            for _, graph, stream in kept:
+                with torch.cuda.stream(stream):
+                    graph.replay()
+                    graph.replay()
+    written = (images[0][0] != images[1][0]) | (images[0][1] != images[1][1])
+    assert written.any() and np.array_equal(images[1][0][written], images[1][1][written])

@@ -576,7 +576,7 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
   }
   if constexpr (D == 2 && EUL && !FT && sizeof(T) == 8) {
     // (off the lattice as well: there in one configuration, whatever is set)
-    if (c->kwide || (P.G.offl && P.G.nv1 <= W2_OFFL_NV && kin2w_lds(P, 4) <= 65536)) {
+    if (c->kwide || (P.G.offl && P.G.nv1 <= W2_OFFL_NV)) {
       dispatch_kin2w(c, a);
       return;
     }

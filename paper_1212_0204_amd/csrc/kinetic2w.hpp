@@ -26,7 +26,11 @@ typedef double w2v __attribute__((ext_vector_type(2)));  // a lane's two pieces
 // its lattice shift (formed once per block, read from LDS as scalars).  256^2 x 32^2 at kinetic CFL 1: the
 // launch 0.216 ms (5.0 TB/s) against 0.244 with one cell per lane, the step
 // 0.262 -> 0.236 ms.
-constexpr int W2_OFFL_NV = 128;  // most nodes per axis then
+// Most nodes per axis then: with 76 the four wavefronts' records and the shifts
+// pass 64 KiB.
+constexpr int W2_OFFL_NV = 72;
+static_assert(4 * (W2_CELLS + W2_OFFL_NV) * row_rec_stride<double>() * 8 + 4 * W2_OFFL_NV <= 65536,
+              "LDS of a block: staged records (four wavefronts) and shifts");
 
 template <int BCX, int UNR, int NG, bool OFFL = false>
 __global__ __launch_bounds__(64 * NG) void k_kinetic2w(StepArgs<double> a, Geom G, int nsegw) {

@@ -913,3 +913,25 @@ def test_captured_steps_between_calls_and_after_the_context(n, prec, euler_befor
                     graph.replay()
     written = (images[0][0] != images[1][0]) | (images[0][1] != images[1][1])
     assert written.any() and np.array_equal(images[1][0][written], images[1][1][written])
+
+
+@gpu
+@pytest.mark.parametrize("n,nv", [((130, 3), 72), ((130, 3), 76), ((130, 3), 80), ((40, 5), 76)])
+def test_2d_offlattice_most_nodes(n, nv):
+    """off-lattice transport about the most nodes per axis whose records and
+    shifts fit a block of the two-cell kernel"""
+    announce("2d off-lattice, most nodes", n, nv)
+    rng = np.random.default_rng(nv)
+    nc = n[0] * n[1]
+    dx, dv = 1.0 / n[0], 10.0 / nv
+    dt = 0.06 * dx / dv
+    fields = (1.0 + 0.1 * rng.uniform(-1, 1, nc), 0.1 * rng.uniform(-1, 1, (2, nc)),
+              1.0 + 0.1 * rng.uniform(-1, 1, nc))
+    o = Oracle(2, n, dx, nv, dv, bc=(1, 0), tau=0.5 * dt, dt=dt)
+    s = _solver(dim=2, n_cells=n, dx=dx, n_vel=nv, dv=dv, bc=(1, 0), tau=0.5 * dt, dt=dt)
+    o.init_macro(*fields)
+    s.set_state_macro(*fields)
+    o.step(4)
+    s.step(4)
+    assert moment_errors(s.read_moments(), o.U, 2).max() < TOL64
+    assert rel_inf(s.read_f(), o.f) < TOL64

@@ -164,7 +164,9 @@ hofks_status hofks_read_tail_substeps(hofks_ctx *ctx, long *n);
  * call) + 1, or during a long hofks_step call the count of a step two behind
  * extended by its trend; a 1D grid of at most 4032 cells (scheme other than
  * 3; in the precision form where lambda < 1e-5) then runs every sub-step in
- * one launch of one block, without a tail.
+ * one launch of one block, without a tail, and any other 1D grid of at most
+ * 256 cells (same schemes) takes k = 1, the tail being one block with its own
+ * barrier.
  * k >= 1 fixes it, so that k = 1 runs every sub-step after the first in the
  * persistent kernel.  The two kernels form the same faces from the same values; their
  * results agree to rounding (the compiler may contract their products

@@ -709,19 +709,29 @@ bool line_shape(const Plan& P, int* cpt, int* nw) {
   return *cpt > 0;
 }
 
+// A 1D grid within one tail block that keeps the per-cell form (see
+// launch_euler): one launch, then every other sub-step in the tail, whose
+// barrier is the block's own.  FP32 200 x 64, lambda 0.13: 83 us per step, 131
+// with a launch per sub-step (100 x 48 67, 97).
+bool tail_of_one_block(const hofks_ctx* c) {
+  return c->P.d == 1 && c->P.GE == 1 && c->desc.scheme != 3 && c->euler_k == 0;
+}
+
 // Whether an untuned 1D step runs its Euler solve before the kinetic kernel on
 // the caller's stream instead of beside it.  The fork and the join cost about
-// as much as a short kinetic launch, so beside pays only for the one-block
-// solve (which leaves the chip to the kinetic kernel) and from more than 64
+// as much as a short kinetic launch, so beside pays only for a solve in one
+// block (which leaves the chip to the kinetic kernel) and from more than 64
 // nodes per axis.  Before against beside, us per step: one block, 200 x 64
-// FP64 38 against 42, 1000 x 16 67, 73, 1000 x 96 77, 73; persistent tail, 3001
-// x 48 FP32 (lambda 0.26) 128, 144, 20000 x 64 154, 171, 60000 x 96 256, 261.
+// FP64 38 against 42, 1000 x 16 67, 73, 1000 x 96 77, 73; tail of one block,
+// FP32 at lambda 0.13, 200 x 16 32, 41, 200 x 64 80, 83, 200 x 96 113, 112,
+// 256 x 256 263, 248; persistent tail, 3001 x 48 FP32 (lambda 0.26) 128, 144,
+// 20000 x 64 154, 171, 60000 x 96 256, 261.
 bool euler_first(const hofks_ctx* c) {
   const Plan& P = c->P;
   int cpt, nw;
   const bool line = c->desc.scheme != 3 && c->euler_k == 0 &&
                     (!P.prec || P.G.lam < LAM_FREE) && line_shape(P, &cpt, &nw);
-  return P.d == 1 && (!line || P.G.nv1 <= 64);
+  return P.d == 1 && (!(line || tail_of_one_block(c)) || P.G.nv1 <= 64);
 }
 
 // Rows per strip of the 2D Euler sub-steps.  Short grids want many strips:
@@ -755,7 +765,7 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     // In the precision form the records and pieces are rounded to FP32, where
     // a last bit of the Euler solve can move a result by 1e-8, so while the
     // pieces carry a part of U^{n+1} (lambda >= LAM_FREE) it keeps the per-cell
-    // form and its bits.
+    // form, with the same split between launches and tail, and its bits.
     const bool free_bits = !P.prec || P.G.lam < LAM_FREE;
     if (c->desc.scheme != 3 && c->euler_k == 0 && free_bits && line_shape(P, &cpt, &nw)) {
 #define KL(C)                                                                                  \
@@ -769,8 +779,9 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
       return;
     }
   }
-  const int K =
-      std::max(1, std::min(c->s_cap, c->euler_k > 0 ? c->euler_k : c->s_next));
+  const int K = std::max(1, std::min(c->s_cap, c->euler_k > 0         ? c->euler_k
+                                               : tail_of_one_block(c) ? 1
+                                                                      : c->s_next));
   if (c->desc.scheme == 3) {  // WENO: three Runge-Kutta stage launches per sub-step
     if constexpr (D == 2) {  // 16 x 16 LDS tiles
       const int ntx = (P.G.n[0] + WT - 1) / WT, nty = (P.G.n[1] + WT - 1) / WT;

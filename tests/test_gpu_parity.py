@@ -935,3 +935,30 @@ def test_2d_offlattice_most_nodes(n, nv):
     s.step(4)
     assert moment_errors(s.read_moments(), o.U, 2).max() < TOL64
     assert rel_inf(s.read_f(), o.f) < TOL64
+
+
+@gpu
+@pytest.mark.parametrize("nx,nv,scheme,tail", [(1, 16, 0, True), (130, 48, 0, True), (200, 96, 0, True),
+                                               (256, 24, 0, True), (257, 24, 0, False),
+                                               (200, 24, 3, False)])
+def test_1d_rows_of_one_tail_block_fp32(nx, nv, scheme, tail):
+    """rows of at most one persistent block in the precision form, lambda not
+    negligible: every sub-step after the first runs behind the block's own
+    barrier, with the bits of one launch before the tail"""
+    announce("1d rows of one tail block", nx, nv, scheme)
+    x = np.arange(nx) * (2 * np.pi / nx)
+    fields = (1.0 + 0.1 * np.sin(x), 0.1 * np.sin(x)[None], 1.0 + 0.1 * np.cos(x))
+    dx, dv = 1.0 / 128, 10.0 / nv
+    o, s = run_pair(1, (nx,), dx, nv, dv, (1,), 0.5 * dx / dv, 1, fields, precision=1, scheme=scheme)
+    assert s.counters()[0] == o.substeps > 2
+    assert s.tail_substeps() == (o.substeps - 1 if tail else 0)
+    o.step(3)
+    s.step(3)
+    assert moment_errors(s.read_moments(), o.U, 1).max() < TOL32
+    if tail:
+        r = _solver(dim=1, n_cells=(nx,), dx=dx, n_vel=nv, dv=dv, bc=(1,), precision=1, scheme=scheme,
+                    tau=0.5 * dx / dv)
+        r.set_euler_launches(1)
+        r.set_state_macro(*fields)
+        r.step(4)
+        assert np.array_equal(s.read_moments(), r.read_moments())

@@ -1,7 +1,9 @@
-// Euler sub-steps on 2D grids (wavefront strips) and 3D grids (LDS tiles).
+// Euler sub-steps on 2D grids (wavefront strips, or LDS tiles on narrow grids)
+// and 3D grids (LDS tiles).
 #pragma once
 #include "dpp.hpp"
 #include "kernels.hpp"
+#include "rules.hpp"
 #include "slope.hpp"
 
 namespace hofks {
@@ -25,8 +27,6 @@ namespace hofks {
 // against the form it replaced (16 x 16 LDS tiles, four slopes per face pair,
 // four block barriers): alone 9.2 -> 5.4 us on 70 x 37 cells, 8.8 -> 6.4 on
 // 256^2, 25.8 -> 12.3 on 512^2.
-constexpr int STRIP_W = 60;
-
 // The flux divergence of the H inner rows of a strip: row(q, U) gives the
 // moments of strip row q (0 .. H + 3, the lane's cell) and done(k, div) takes
 // twice the divergence (times dx) of inner row k as soon as it is complete.
@@ -180,6 +180,131 @@ __global__ __launch_bounds__(256, H == 1 && sizeof(T) == 4 ? 5 : 1) void k_euler
       });
   if (!phys) atomicOr(a.flag, FLAG_NONPHYS);
   if (i + 1 < s) fold_speeds(S, i + 1, lane, wv, mx);
+}
+
+// The same sub-step with LDS tiles, for grids whose rows leave most lanes of
+// the strips idle (see `euler_tiles`): a block loads a 16 x 16 tile of cells
+// with two halo cells on every side, then for each axis in turn evaluates the
+// split fluxes of the cells the faces along that axis need (x: 20 x 16, y:
+// 16 x 20) into one buffer, every thread adding the difference of its cell's
+// two faces along that axis; then the new value.  The same bits as the strips.
+//
+// Bound by its block barriers and LDS round trips on such grids (25.8 us per
+// sub-step on 512^2, 8.8 on 256^2, against the strips' 12.3 and 6.4).
+constexpr int EH = ET + 4;  // tile edge with two halo cells on each side
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_euler_sub_tile(StepArgs<T> a, Geom G, int i, int ntx) {
+  constexpr int NM = 4;
+  double* S = a.set_r;
+  const int Nx = G.n[0], Ny = G.n[1];
+  // contiguous ranges of tiles per die (blocks reach the dies round-robin),
+  // so that the halo of most tiles was written on the same die
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int X0 = (tile % ntx) * ET, Y0 = (tile / ntx) * ET;
+  const int t = threadIdx.x;
+  const double* in = (i == 0) ? a.U_in : ((i & 1) ? a.UE1 : a.UE0);
+  double* out = ((i + 1) & 1) ? a.UE1 : a.UE0;
+
+  __shared__ double Ut[NM][EH][EH];
+  // split fluxes along one axis at a time (x, then y) in one buffer:
+  // x: [+/-][r][y][x + 2] over 16 x 20 cells; y: [+/-][r][y + 2][x] over 20 x 16
+  __shared__ double Wb[2][NM][ET * EH];
+
+  // tile + halo (periodic wrap or outflow clamp, as the per-cell form),
+  // loaded before the speeds of the sub-step are read so that the two
+  // memory round trips overlap (both buffers exist whatever s is)
+  constexpr int NQ = (EH * EH + 255) / 256;
+  double Uload[NQ][NM];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + k * 256;
+    if (q < EH * EH) {
+      const int hx = q % EH, hy = q / EH;
+      const int gx = map_axis(X0 + hx - 2, Nx, G.bc[0]);
+      const int gy = map_axis(Y0 + hy - 2, Ny, G.bc[1]);
+      const size_t j = (size_t)gy * Nx + gx;
+#pragma unroll
+      for (int r = 0; r < NM; ++r) Uload[k][r] = in[(size_t)r * G.nc + j];
+    }
+  }
+  double alpha[2];
+  strip_speeds(S, i, t & 63, alpha);
+  // the count: formed by sub-step 0, which records it for the later launches
+  const int s = i == 0 ? open_substeps<2>(a, G) : a.flag[1];
+  if (i >= s) return;
+  const double dts_dx = (G.dt / s) / G.dx;
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const int q = t + k * 256;
+    if (q < EH * EH) {
+#pragma unroll
+      for (int r = 0; r < NM; ++r) Ut[r][q / EH][q % EH] = Uload[k][r];
+    }
+  }
+  __syncthreads();
+  bool phys = true;
+  const int lx = t % ET, ly = t / ET;
+  const int gx = X0 + lx, gy = Y0 + ly;
+  const bool own = gx < Nx && gy < Ny;
+  double div[NM] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int ax = 0; ax < 2; ++ax) {
+    if (ax == 1) __syncthreads();  // the x faces have been read
+    // fluxes along ax: x for cells (x = -2..17, y = 0..15), y for (x = 0..15, y = -2..17)
+    for (int q = t; q < ET * EH; q += blockDim.x) {
+      const int hx = ax == 0 ? q % EH : q % ET + 2;
+      const int hy = ax == 0 ? q / EH + 2 : q / ET;
+      double Uq[NM];
+#pragma unroll
+      for (int r = 0; r < NM; ++r) Uq[r] = Ut[r][hy][hx];
+      double Wp[NM], Wm[NM];
+      phys &= split_flux<2>(Uq, ax, alpha[ax], G.gam, Wp, Wm);
+#pragma unroll
+      for (int r = 0; r < NM; ++r) {
+        Wb[0][r][q] = Wp[r];
+        Wb[1][r][q] = Wm[r];
+      }
+    }
+    __syncthreads();
+    if (own) {
+#pragma unroll
+      for (int r = 0; r < NM; ++r) {
+        // cells l-2 .. l+2 along ax: x -> entries ly*EH + lx + k, y -> (ly + k)*ET + lx
+        double wp[5], wm[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+          const int e = ax == 0 ? ly * EH + lx + k : (ly + k) * ET + lx;
+          wp[k] = Wb[0][r][e];
+          wm[k] = Wb[1][r][e];
+        }
+        const double spl = vl_slope(wp[1] - wp[0], wp[2] - wp[1], a.unlimited);
+        const double sml = vl_slope(wm[2] - wm[1], wm[3] - wm[2], a.unlimited);
+        const double spr = vl_slope(wp[2] - wp[1], wp[3] - wp[2], a.unlimited);
+        const double smr = vl_slope(wm[3] - wm[2], wm[4] - wm[3], a.unlimited);
+        const double psil = 0.5 * (wp[1] + wm[2]) + 0.25 * (spl - sml);
+        const double psir = 0.5 * (wp[2] + wm[3]) + 0.25 * (spr - smr);
+        div[r] += psir - psil;
+      }
+    }
+  }
+  double mx[2] = {0.0, 0.0};
+  if (own) {
+    double Un[NM];
+#pragma unroll
+    for (int r = 0; r < NM; ++r) Un[r] = Ut[r][ly + 2][lx + 2] - dts_dx * div[r];
+    const size_t j = (size_t)gy * Nx + gx;
+#pragma unroll
+    for (int r = 0; r < NM; ++r) out[(size_t)r * G.nc + j] = Un[r];
+    if (i + 1 < s) {
+      double sp[3];
+      phys &= lf_speeds<2>(Un, G.gam, sp);
+      mx[0] = sp[0];
+      mx[1] = sp[1];
+    }
+  }
+  if (!phys) atomicOr(a.flag, FLAG_NONPHYS);
+  if (i + 1 < s) fold_speeds(S, i + 1, t & 63, t >> 6, mx);
 }
 
 // Euler sub-step on a 3D grid with LDS tiles: one block of 256 threads

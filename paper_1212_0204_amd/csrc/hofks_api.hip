@@ -744,8 +744,7 @@ bool euler_first(const hofks_ctx* c) {
 // 512^2 alone 15.5 us with one row, 12.8 with three, 14.4 with four (288
 // blocks) and 12.3 with five (234 blocks).
 int strip_rows(const Plan& P) {
-  const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
-  auto blocks = [&](int H) { return nsx * ((P.G.n[1] + 4 * H - 1) / (4 * H)); };
+  auto blocks = [&](int H) { return strip_blocks(P.G.n[0], P.G.n[1], H); };
   if (blocks(1) <= 2 * P.ncu) return 1;
   if (blocks(2) <= P.ncu) return 2;
   return blocks(3) <= P.ncu ? 3 : 5;
@@ -798,15 +797,19 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     hipLaunchKernelGGL((k_weno_tail<D, T, 256>), dim3(P.GE), dim3(256), 0, st, a, P.G, K);
     return;
   }
-  if constexpr (D == 2) {  // wavefront strips of 60 x H cells
+  if constexpr (D == 2) {  // 16 x 16 LDS tiles or wavefront strips of 60 x H cells
+    const bool tiles = euler_tiles(P.G.n[0], P.G.n[1], P.ncu);
+    const int ntx = (P.G.n[0] + ET - 1) / ET, nty = (P.G.n[1] + ET - 1) / ET;
+    for (int i = 0; tiles && i < K; ++i)
+      hipLaunchKernelGGL((k_euler_sub_tile<T>), dim3(ntx * nty), dim3(256), 0, st, a, P.G, i, ntx);
     const int H = strip_rows(P);
     const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
-    const unsigned nb = (unsigned)(nsx * ((P.G.n[1] + 4 * H - 1) / (4 * H)));
+    const unsigned nb = (unsigned)strip_blocks(P.G.n[0], P.G.n[1], H);
 #define KE(HH, U)                                                                              \
   hipLaunchKernelGGL((k_euler_strip<T, HH, U>), dim3(nb), dim3(256), 0, st, a, P.G, i, nsx)
 #define KH(HH) \
   if (a.unlimited) KE(HH, true); else KE(HH, false);
-    for (int i = 0; i < K; ++i) {
+    for (int i = 0; !tiles && i < K; ++i) {
       if (H == 1) { KH(1) } else if (H == 2) { KH(2) } else if (H == 3) { KH(3) } else { KH(5) }
     }
 #undef KH

@@ -962,3 +962,25 @@ def test_1d_rows_of_one_tail_block_fp32(nx, nv, scheme, tail):
         r.set_state_macro(*fields)
         r.step(4)
         assert np.array_equal(s.read_moments(), r.read_moments())
+
+
+@gpu
+@pytest.mark.parametrize("n,bc,scheme,prec", [
+    ((4, 1030), (0, 0), 0, 0), ((15, 1041), (1, 1), 2, 0), ((16, 1029), (0, 1), 0, 1),  # one tile a row
+    ((1, 1100), (1, 0), 0, 0), ((17, 1090), (1, 0), 0, 1),                              # a ragged second
+    ((64, 530), (0, 0), 0, 0),                                                          # four of them
+])
+def test_2d_tiles_on_narrow_grids(n, bc, scheme, prec):
+    """the LDS tiles of the 2D Euler sub-steps, which narrow grids with more
+    strips than compute units take"""
+    announce("2d tiles", n, bc, scheme, prec)
+    rng = np.random.default_rng(n[0] + n[1])
+    nc = n[0] * n[1]
+    rho = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    th = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    u = 0.1 * rng.uniform(-1, 1, (2, nc))
+    dx = 1.0 / max(n)
+    o, s = run_pair(2, n, dx, 8, 0.75, bc, 0.2 * dx, 2, (rho, u, th), precision=prec, scheme=scheme)
+    err = moment_errors(s.read_moments(), o.U, 2)
+    assert err.max() < (TOL64 if prec == 0 else TOL32), err
+    assert s.counters()[0] == o.substeps

@@ -1,0 +1,32 @@
+"""The size rules of the 2D dispatch (plain C++), compiled on the CPU: each
+listed grid takes the kernel that measured faster on 256 compute units."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_1212_0204_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "r.cpp").write_text('''#include "rules.hpp"
+extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny, ncu); }
+''')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "r.so"),
+                    str(d / "r.cpp")], check=True)
+    return ctypes.CDLL(str(d / "r.so"))
+
+
+@pytest.mark.parametrize("n,tiles", [
+    ((4, 4096), 1), ((8, 8192), 1), ((16, 4096), 1), ((16, 16384), 1), ((20, 3276), 1), ((32, 2048), 1),
+    ((32, 4096), 1), ((64, 1024), 1), ((64, 2048), 1),
+    # few strips, lanes mostly busy, or several rounds of them
+    ((8, 1024), 0), ((16, 1024), 0), ((32, 1024), 0), ((64, 512), 0), ((40, 1638), 0), ((48, 5461), 0),
+    ((72, 910), 0), ((122, 537), 0), ((32, 8192), 0), ((64, 4096), 0), ((70, 37), 0), ((256, 256), 0),
+    ((512, 512), 0), ((20000, 1), 0), ((4096, 4), 0)])
+def test_euler_tiles_on_narrow_grids(rules, n, tiles):
+    assert rules.tiles(n[0], n[1], 256) == tiles

@@ -472,20 +472,10 @@ int kin_unroll_euler(const Plan& P, int ng, int unr) {
 // so the order of sums that are then rounded to FP32 is free.
 constexpr double LAM_FREE = 1e-5;
 
-// Wavefronts of an untuned 2D FP32 step while the order of its sums is free,
-// from the blocks of the launch per compute unit (four with 16 loads ahead,
-// the others with eight).  Between two and five the launch is little more
-// than a round and two wavefronts leave the Euler blocks room beside them
-// (256^2 x 32^2, 1024 blocks: 0.183 ms per step with two, 0.212 with four,
-// 0.247 with eight; 300 x 256 x 32^2 0.263, 0.267, 0.299); in many rounds a
-// block of eight ends sooner and frees room for a whole Euler block at once
-// (400^2 x 32^2, 2800 blocks: 0.436, 0.453 with four, 0.457 with two; 512^2 x
-// 32^2 0.711, 0.762, 0.774).  In between and below four are as good or better
-// (330 x 300 x 32^2, 1800 blocks: 0.385, 0.404 with eight, 0.439 with two; 200
-// x 120 x 32^2, 480 blocks: 0.139, 0.152, 0.142).
-int fp32_wavefronts(const Plan& P, unsigned nb) {
-  const unsigned cu = P.ncu;
-  const int ng = nb > 10 * cu ? 8 : nb > 2 * cu && nb <= 5 * cu ? 2 : 4;
+// Wavefronts of an untuned 2D FP32 step while the order of its sums is free
+// (four with 16 loads ahead, the others with eight)
+int untuned_wavefronts(const Plan& P, unsigned nb) {
+  const int ng = fp32_wavefronts(P.G.n[0], P.G.nv1, nb, P.ncu);
   return kin_lds(P, ng) <= 65536 ? ng : 2;
 }
 
@@ -598,7 +588,7 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
   int ng = c->kng, want = c->kunr;
   if constexpr (D == 2 && CP)
     if (c->cfg_auto && P.G.lam < LAM_FREE && P.G.nv1 % 8 == 0) {
-      ng = fp32_wavefronts(P, grid.x);
+      ng = untuned_wavefronts(P, grid.x);
       if (ng != 4) want = 8;
     }
   int unr = kin_unroll_euler(P, ng, want);

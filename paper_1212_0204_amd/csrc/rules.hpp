@@ -1,5 +1,5 @@
-// rules.hpp -- which of two kernels with the same bits a 2D step takes, from
-// the sizes of the grid and the compute units of the chip (plain C++).
+// rules.hpp -- which kernel or launch shape an untuned 2D step takes, from the
+// sizes of the grid and the compute units of the chip (plain C++).
 #pragma once
 
 namespace hofks {
@@ -25,6 +25,27 @@ inline bool euler_tiles(int nx, int ny, int ncu) {
   const int nsx = (nx + STRIP_W - 1) / STRIP_W, ntx = (nx + ET - 1) / ET;
   return strip_blocks(nx, ny, 1) > ncu &&
          (ntx <= nsx || (ntx <= 2 * nsx && strip_blocks(nx, ny, 5) <= ncu));
+}
+
+// Wavefronts per block of a 2D FP32 kinetic launch of nb blocks, by blocks per
+// compute unit.  Between two and five the launch is little more than a round
+// and two wavefronts leave the Euler blocks room beside them (256^2 x 32^2, 1024
+// blocks: 0.183 ms per step with two, 0.212 with four, 0.247 with eight; 300 x
+// 256 x 32^2 0.263, 0.267, 0.299).  In many rounds a block of eight ends sooner
+// and frees room for a whole Euler block at once (400^2 x 32^2, 2800 blocks:
+// 0.436, 0.453 with four, 0.457 with two; 512^2 x 32^2 0.711, 0.762, 0.774), if
+// its wavefronts have work enough for that: not on rows short of a segment (16
+// x 5120, eight against four: 16^2 0.233, 0.189, 32^2 0.583, 0.492, 64^2 1.925,
+// 1.409), not with 8^2 nodes (200 x 1280 0.164, 0.147), and with 16^2 and 24^2
+// only up to about 1.25 blocks per unit and node (512 x 960 x 16^2, 30 per
+// unit, 0.492, 0.465; 128 x 5120 x 24^2, 40, 1.138, 1.054; 512 x 2048 x 32^2,
+// 64, 2.72, 2.90).  Else four are as good or better (330 x 300 x 32^2, 1800
+// blocks: 0.385, 0.404 with eight, 0.439 with two; 200 x 120 x 32^2, 480
+// blocks: 0.139, 0.152, 0.142).
+inline int fp32_wavefronts(int nx, int nv, long nb, int ncu) {
+  if (nb > 2L * ncu && nb <= 5L * ncu) return 2;
+  const bool busy = nx >= 64 && nv >= 16 && (nv >= 32 || 4 * nb <= 5L * nv * ncu);
+  return nb > 10L * ncu && busy ? 8 : 4;
 }
 
 }  // namespace hofks

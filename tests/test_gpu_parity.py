@@ -984,3 +984,20 @@ def test_2d_tiles_on_narrow_grids(n, bc, scheme, prec):
     err = moment_errors(s.read_moments(), o.U, 2)
     assert err.max() < (TOL64 if prec == 0 else TOL32), err
     assert s.counters()[0] == o.substeps
+
+
+@gpu
+@pytest.mark.parametrize("n,nv", [((63, 2570), 16), ((64, 2570), 16), ((64, 5130), 16)])
+def test_2d_fp32_wavefronts_in_many_rounds(n, nv):
+    """blocks of four and of eight wavefronts on 2D FP32 grids of many rounds,
+    on either side of the lines between them"""
+    announce("2d fp32 wavefronts", n, nv)
+    rng = np.random.default_rng(n[0])
+    nc, dx, dv = n[0] * n[1], 1.0 / 128, 10.0 / nv
+    x = np.arange(nc) * (2 * np.pi / nc)
+    rho = 1.0 + 0.1 * np.sin(x) + 0.02 * rng.uniform(-1, 1, nc)
+    th = 1.0 + 0.1 * np.cos(x) + 0.02 * rng.uniform(-1, 1, nc)
+    o, s = run_pair(2, n, dx, nv, dv, (1, 0), 0.05 * dx / dv, 1, (rho, 0.1 * np.sin(x) * np.ones((2, 1)), th),
+                    precision=1)
+    assert moment_errors(s.read_moments(), o.U, 2).max() < TOL32
+    assert s.counters()[0] == o.substeps

@@ -15,6 +15,9 @@ def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "r.cpp").write_text('''#include "rules.hpp"
 extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny, ncu); }
+extern "C" int wavefronts(int nx, int ny, int nv, int ncu) {
+  return hofks::fp32_wavefronts(nx, nv, (long)((nx + 63) / 64) * ny, ncu);
+}
 ''')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "r.so"),
                     str(d / "r.cpp")], check=True)
@@ -30,3 +33,15 @@ extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny
     ((512, 512), 0), ((20000, 1), 0), ((4096, 4), 0)])
 def test_euler_tiles_on_narrow_grids(rules, n, tiles):
     assert rules.tiles(n[0], n[1], 256) == tiles
+
+
+@pytest.mark.parametrize("n,nv,w", [
+    ((256, 256), 32, 2), ((300, 256), 32, 2), ((330, 300), 32, 4), ((200, 120), 32, 4),
+    ((400, 400), 32, 8), ((512, 512), 32, 8), ((330, 853), 16, 8), ((200, 1024), 16, 8),
+    ((70, 3840), 24, 8), ((512, 2048), 32, 8), ((128, 3840), 40, 8),
+    # wavefronts without work enough in blocks of eight
+    ((4, 20000), 8, 4), ((16, 5120), 16, 4), ((48, 5120), 24, 4), ((16, 3072), 32, 4), ((16, 4096), 64, 4),
+    ((200, 1280), 8, 4), ((400, 1462), 8, 4), ((512, 960), 16, 4), ((128, 5120), 16, 4),
+    ((128, 5120), 24, 4)])
+def test_fp32_wavefronts(rules, n, nv, w):
+    assert rules.wavefronts(n[0], n[1], nv, 256) == w

@@ -724,22 +724,6 @@ bool euler_first(const hofks_ctx* c) {
   return P.d == 1 && (!(line || tail_of_one_block(c)) || P.G.nv1 <= 64);
 }
 
-// Rows per strip of the 2D Euler sub-steps.  Short grids want many strips:
-// with one row a sub-step alone takes 5.4 us on 70 x 37 cells and 6.4 on
-// 256^2 (two rows: 6.5 and 6.3, and beside the kinetic kernel 17.5 -> 21.1 on
-// 256^2, where the longer chain of a wavefront shows), up to two blocks per
-// compute unit.  Larger grids are bound by the FP64 issue rate, where more
-// rows share more of the y fluxes and slopes, and by the last round of
-// blocks, so the fewest rows that give each compute unit at most one block:
-// 512^2 alone 15.5 us with one row, 12.8 with three, 14.4 with four (288
-// blocks) and 12.3 with five (234 blocks).
-int strip_rows(const Plan& P) {
-  auto blocks = [&](int H) { return strip_blocks(P.G.n[0], P.G.n[1], H); };
-  if (blocks(1) <= 2 * P.ncu) return 1;
-  if (blocks(2) <= P.ncu) return 2;
-  return blocks(3) <= P.ncu ? 3 : 5;
-}
-
 // Euler solve of a step: one launch per sub-step for the first K = (last
 // known count + a margin, see plan_launches) sub-steps (the kernel boundary is
 // the grid-wide barrier), then a persistent tail that runs any further
@@ -792,15 +776,16 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     const int ntx = (P.G.n[0] + ET - 1) / ET, nty = (P.G.n[1] + ET - 1) / ET;
     for (int i = 0; tiles && i < K; ++i)
       hipLaunchKernelGGL((k_euler_sub_tile<T>), dim3(ntx * nty), dim3(256), 0, st, a, P.G, i, ntx);
-    const int H = strip_rows(P);
+    const int H = strip_rows(P.G.n[0], P.G.n[1], sizeof(T) == 4, P.ncu);
     const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
     const unsigned nb = (unsigned)strip_blocks(P.G.n[0], P.G.n[1], H);
 #define KE(HH, U)                                                                              \
   hipLaunchKernelGGL((k_euler_strip<T, HH, U>), dim3(nb), dim3(256), 0, st, a, P.G, i, nsx)
 #define KH(HH) \
   if (a.unlimited) KE(HH, true); else KE(HH, false);
+    constexpr int HM = sizeof(T) == 4 ? 2 : 4;  // the rows that only one of the two takes
     for (int i = 0; !tiles && i < K; ++i) {
-      if (H == 1) { KH(1) } else if (H == 2) { KH(2) } else if (H == 3) { KH(3) } else { KH(5) }
+      if (H == 1) { KH(1) } else if (H == HM) { KH(HM) } else if (H == 3) { KH(3) } else { KH(5) }
     }
 #undef KH
 #undef KE

@@ -12,6 +12,31 @@ inline long strip_blocks(int nx, int ny, int rows) {
   return (long)((nx + STRIP_W - 1) / STRIP_W) * ((ny + 4 * rows - 1) / (4 * rows));
 }
 
+// Rows per strip.  Short grids want many strips: with one row a sub-step alone
+// takes 5.4 us on 70 x 37 cells and 6.4 on 256^2 (two rows: 6.5 and 6.3, and
+// beside the kinetic kernel 17.5 -> 21.1 on 256^2, where the longer chain of a
+// wavefront shows).  Alone, larger grids are bound by the FP64 issue rate,
+// where more rows share more of the y fluxes and slopes, and by the last round
+// of blocks (512^2 15.5 us with one row, 12.8 with three, 14.4 with four in 288
+// blocks, 12.3 with five in 234).  What counts is the step, us:
+// - beside FP64 pieces one row pays up to 2.5 blocks per compute unit, and up to
+//   3.25 where more than a quarter of the lanes are idle, since blocks that end
+//   soon keep fewer kinetic blocks out (256 x 512 x 32^2 543, 608 with three,
+//   638 with five; 320 x 343 x 24^2 330, 365; 72 x 1527 x 32^2 615, 686; but 400^2
+//   x 32^2, 2.7, 824, 770); then the fewest rows that give each unit at most one
+//   block (364 x 467 x 32^2 776 with four, 791 with five), and five;
+// - beside FP32 pieces three rows where those do (256 x 512 x 16^2 166, 180 with
+//   one), else two up to two blocks per unit (128 x 1024 x 32^2 428, 462 with
+//   five; 364 x 467 x 32^2 520, 598), and five.
+inline int strip_rows(int nx, int ny, bool fp32, int ncu) {
+  const long b1 = strip_blocks(nx, ny, 1);
+  const bool idle = 4L * nx < 3L * STRIP_W * ((nx + STRIP_W - 1) / STRIP_W);
+  if (4 * b1 <= (fp32 ? 8L : idle ? 13L : 10L) * ncu) return 1;
+  if (strip_blocks(nx, ny, 3) <= ncu) return 3;
+  if (fp32) return strip_blocks(nx, ny, 2) <= 2L * ncu ? 2 : 5;
+  return strip_blocks(nx, ny, 4) <= ncu ? 4 : 5;
+}
+
 // Whether the 2D Euler sub-steps run by 16 x 16 tiles instead of strips: where
 // most lanes of the strips are idle (up to 16 cells in a row, or up to two
 // tiles per strip: 17 .. 32 and 61 .. 64) and there are more strips than

@@ -1001,3 +1001,22 @@ def test_2d_fp32_wavefronts_in_many_rounds(n, nv):
                     precision=1)
     assert moment_errors(s.read_moments(), o.U, 2).max() < TOL32
     assert s.counters()[0] == o.substeps
+
+
+@gpu
+@pytest.mark.parametrize("n,prec", [((330, 345), 0), ((130, 1009), 0), ((395, 411), 0), ((365, 470), 0),
+                                    ((513, 517), 0), ((330, 345), 1), ((125, 1061), 1), ((513, 517), 1)])
+def test_2d_rows_per_strip(n, prec):
+    """strips of one to five rows on grids of about a hundred thousand cells,
+    none of them a multiple of the strips"""
+    announce("2d rows per strip", n, prec)
+    rng = np.random.default_rng(n[0])
+    nc = n[0] * n[1]
+    rho = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    th = 1.0 + 0.1 * rng.uniform(-1, 1, nc)
+    u = 0.1 * rng.uniform(-1, 1, (2, nc))
+    dx = 1.0 / max(n)
+    o, s = run_pair(2, n, dx, 6, 1.0, (0, 1), 0.2 * dx, 2, (rho, u, th), precision=prec)
+    err = moment_errors(s.read_moments(), o.U, 2)
+    assert err.max() < (TOL64 if prec == 0 else TOL32), err
+    assert s.counters()[0] == o.substeps

@@ -15,6 +15,7 @@ def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "r.cpp").write_text('''#include "rules.hpp"
 extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny, ncu); }
+extern "C" int rows(int nx, int ny, int fp32, int ncu) { return hofks::strip_rows(nx, ny, fp32, ncu); }
 extern "C" int wavefronts(int nx, int ny, int nv, int ncu) {
   return hofks::fp32_wavefronts(nx, nv, (long)((nx + 63) / 64) * ny, ncu);
 }
@@ -45,3 +46,14 @@ def test_euler_tiles_on_narrow_grids(rules, n, tiles):
     ((128, 5120), 24, 4)])
 def test_fp32_wavefronts(rules, n, nv, w):
     assert rules.wavefronts(n[0], n[1], nv, 256) == w
+
+
+@pytest.mark.parametrize("n,fp64,fp32", [
+    ((70, 37), 1, 1), ((256, 256), 1, 1), ((320, 300), 1, 1),
+    # past two blocks of one row per compute unit
+    ((320, 343), 1, 3), ((200, 550), 1, 3), ((256, 512), 1, 3), ((350, 350), 1, 3),
+    ((72, 1527), 1, 3), ((128, 1024), 1, 2), ((122, 1074), 1, 2),  # a quarter of the lanes idle
+    ((400, 400), 3, 3), ((364, 467), 4, 2), ((450, 450), 4, 2),
+    ((512, 512), 5, 5), ((1000, 1000), 5, 5)])
+def test_rows_per_strip(rules, n, fp64, fp32):
+    assert (rules.rows(n[0], n[1], 0, 256), rules.rows(n[0], n[1], 1, 256)) == (fp64, fp32)

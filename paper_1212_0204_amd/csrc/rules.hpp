@@ -40,16 +40,17 @@ inline int strip_rows(int nx, int ny, bool fp32, int ncu) {
 // Whether the 2D Euler sub-steps run by 16 x 16 tiles instead of strips: where
 // most lanes of the strips are idle (up to 16 cells in a row, or up to two
 // tiles per strip: 17 .. 32 and 61 .. 64) and there are more strips than
-// compute units, so that the idle lanes cost time.  With more strips than one
-// round of the tallest, the second kind is as fast by strips.  Tiles against
-// strips, us per step (16^2 nodes), FP64 and FP32: 16 x 4096 380 against 410, 190
-// against 226; 4 x 4096 360, 386, 167, 204; 32 x 4096 419, 431, 220, 243; 64 x
-// 1024 153, 171, 121, 125; on the other side 16 x 1024 140, 122, 112, 98; 64 x 512
-// 127, 113, 113, 103; 32 x 8192 805, 829, 461, 439; 40 x 1638 211, 206, 149, 133.
+// compute units, so that the idle lanes cost time.  In more than two rounds of
+// the tallest strips the second kind is as fast by them.  Tiles against strips,
+// us per step with 16^2 nodes, FP64 and FP32: 16 x 4096 380 against 410, 166, 224;
+// 4 x 4096 360, 386, 151, 208; 24 x 5461 544, 560, 250, 298; 32 x 8192 805, 829,
+// 353, 380; 64 x 1024 153, 171, 122, 126; on the other side 16 x 1024 140, 122,
+// 113, 98; 64 x 512 127, 113, 113, 102; 20 x 13107 1266, 1266, 563, 548; 40 x 1638
+// 211, 206, 149, 134.
 inline bool euler_tiles(int nx, int ny, int ncu) {
   const int nsx = (nx + STRIP_W - 1) / STRIP_W, ntx = (nx + ET - 1) / ET;
   return strip_blocks(nx, ny, 1) > ncu &&
-         (ntx <= nsx || (ntx <= 2 * nsx && strip_blocks(nx, ny, 5) <= ncu));
+         (ntx <= nsx || (ntx <= 2 * nsx && strip_blocks(nx, ny, 5) <= 2L * ncu));
 }
 
 // Wavefronts per block of a 2D FP32 kinetic launch of nb blocks, by blocks per

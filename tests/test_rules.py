@@ -27,10 +27,10 @@ extern "C" int wavefronts(int nx, int ny, int nv, int ncu) {
 
 @pytest.mark.parametrize("n,tiles", [
     ((4, 4096), 1), ((8, 8192), 1), ((16, 4096), 1), ((16, 16384), 1), ((20, 3276), 1), ((32, 2048), 1),
-    ((32, 4096), 1), ((64, 1024), 1), ((64, 2048), 1),
+    ((32, 4096), 1), ((64, 1024), 1), ((64, 2048), 1), ((24, 5461), 1), ((32, 8192), 1),
     # few strips, lanes mostly busy, or several rounds of them
     ((8, 1024), 0), ((16, 1024), 0), ((32, 1024), 0), ((64, 512), 0), ((40, 1638), 0), ((48, 5461), 0),
-    ((72, 910), 0), ((122, 537), 0), ((32, 8192), 0), ((64, 4096), 0), ((70, 37), 0), ((256, 256), 0),
+    ((72, 910), 0), ((122, 537), 0), ((20, 13107), 0), ((64, 8192), 0), ((70, 37), 0), ((256, 256), 0),
     ((512, 512), 0), ((20000, 1), 0), ((4096, 4), 0)])
 def test_euler_tiles_on_narrow_grids(rules, n, tiles):
     assert rules.tiles(n[0], n[1], 256) == tiles

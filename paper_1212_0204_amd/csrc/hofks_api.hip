@@ -565,8 +565,9 @@ void dispatch_kin(hofks_ctx* c, const StepArgs<T>& a, dim3 grid) {
     }
   }
   if constexpr (D == 2 && EUL && !FT && sizeof(T) == 8) {
-    // (off the lattice as well: there in one configuration, whatever is set)
-    if (c->kwide || (P.G.offl && P.G.nv1 <= W2_OFFL_NV)) {
+    // (off the lattice there is one configuration, whatever is set)
+    if (c->kwide || (P.G.offl && P.G.nv1 <= W2_OFFL_NV &&
+                     offlattice_pairs(P.G.n[0], P.G.n[1], P.ncu))) {
       dispatch_kin2w(c, a);
       return;
     }

@@ -19,7 +19,6 @@
 
 namespace hofks {
 
-constexpr int W2_CELLS = 128;  // cells per block row segment
 typedef double w2v __attribute__((ext_vector_type(2)));  // a lane's two pieces
 
 // OFFL: a free time step; the shift of a velocity node in this step replaces

@@ -6,6 +6,7 @@ namespace hofks {
 
 constexpr int STRIP_W = 60;    // cells that an Euler strip advances in x
 constexpr int ET = 16;         // edge of an Euler tile
+constexpr int W2_CELLS = 128;  // cells per block row segment of the two-cell kinetic kernel
 
 // blocks of a sub-step by strips of `rows` rows, four to a block
 inline long strip_blocks(int nx, int ny, int rows) {
@@ -72,6 +73,22 @@ inline int fp32_wavefronts(int nx, int nv, long nb, int ncu) {
   if (nb > 2L * ncu && nb <= 5L * ncu) return 2;
   const bool busy = nx >= 64 && nv >= 16 && (nv >= 32 || 4 * nb <= 5L * nv * ncu);
   return nb > 10L * ncu && busy ? 8 : 4;
+}
+
+// Whether an off-lattice 2D FP64 step runs in the two-cell kinetic kernel (128
+// cells of a row to a block) instead of the general one (64): where a launch is
+// more than one block per compute unit and has half as many per unit, to 8%, as
+// the general one.  A lane's second cell doubles its chain, which shows while a
+// unit holds one block, and is wasted on ragged rows.  General against two-cell
+// kernel, us per step, blocks per unit rounded up: 256^2 x 32^2 (4, 2) 273, 242;
+// 384 x 256 x 32^2 (6, 3) 396, 375; 360 x 400 x 32^2 (10, 5) 614, 563; on the
+// other side 150^2 x 16^2 (2, 2) 57, 78; 64^2 x 64^2 (1, 1) 313, 558; 450 x 64 x
+// 32^2 (2, 1) 148, 187; 150 x 400 x 32^2 (5, 4) 339, 432; 300 x 128 x 32^2 (3, 2)
+// 196, 217; 256 x 400 x 32^2 (7, 4) 430, 467.
+inline bool offlattice_pairs(int nx, int ny, int ncu) {
+  const long two = ((long)((nx + W2_CELLS - 1) / W2_CELLS) * ny + ncu - 1) / ncu;
+  const long one = ((long)((nx + 63) / 64) * ny + ncu - 1) / ncu;
+  return two > 1 && 20 * one >= 37 * two;
 }
 
 }  // namespace hofks

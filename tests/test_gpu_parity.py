@@ -1020,3 +1020,28 @@ def test_2d_rows_per_strip(n, prec):
     err = moment_errors(s.read_moments(), o.U, 2)
     assert err.max() < (TOL64 if prec == 0 else TOL32), err
     assert s.counters()[0] == o.substeps
+
+
+@gpu
+@pytest.mark.parametrize("n,nv,bc", [((65, 512), 16, (0, 0)), ((255, 512), 4, (1, 0)), ((250, 256), 12, (0, 1)),
+                                     ((65, 512), 72, (1, 0)),  # (one step)
+                                     ((129, 700), 8, (1, 1)), ((191, 320), 16, (0, 1))])
+def test_2d_offlattice_pairs_on_many_blocks(n, nv, bc):
+    """off-lattice transport on grids of more than one block per compute unit,
+    in the two-cell kernel where it halves the blocks and in the general one"""
+    announce("2d off-lattice pairs, many blocks", n, nv, bc)
+    rng = np.random.default_rng(nv)
+    nc = n[0] * n[1]
+    dx, dv = 1.0 / n[0], 10.0 / max(nv, 8)
+    dt = 0.21 * dx / dv
+    fields = (1.0 + 0.1 * rng.uniform(-1, 1, nc), 0.1 * rng.uniform(-1, 1, (2, nc)),
+              1.0 + 0.1 * rng.uniform(-1, 1, nc))
+    o = Oracle(2, n, dx, nv, dv, bc=bc, tau=0.5 * dt, dt=dt)
+    s = _solver(dim=2, n_cells=n, dx=dx, n_vel=nv, dv=dv, bc=bc, tau=0.5 * dt, dt=dt)
+    o.init_macro(*fields)
+    s.set_state_macro(*fields)
+    o.step(1 if nv == 72 else 2)
+    s.step(1 if nv == 72 else 2)
+    assert moment_errors(s.read_moments(), o.U, 2).max() < TOL64
+    if nv < 72:
+        assert rel_inf(s.read_f(), o.f) < TOL64

@@ -15,6 +15,7 @@ def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "r.cpp").write_text('''#include "rules.hpp"
 extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny, ncu); }
+extern "C" int pairs(int nx, int ny, int ncu) { return hofks::offlattice_pairs(nx, ny, ncu); }
 extern "C" int rows(int nx, int ny, int fp32, int ncu) { return hofks::strip_rows(nx, ny, fp32, ncu); }
 extern "C" int wavefronts(int nx, int ny, int nv, int ncu) {
   return hofks::fp32_wavefronts(nx, nv, (long)((nx + 63) / 64) * ny, ncu);
@@ -57,3 +58,11 @@ def test_fp32_wavefronts(rules, n, nv, w):
     ((512, 512), 5, 5), ((1000, 1000), 5, 5)])
 def test_rows_per_strip(rules, n, fp64, fp32):
     assert (rules.rows(n[0], n[1], 0, 256), rules.rows(n[0], n[1], 1, 256)) == (fp64, fp32)
+
+
+@pytest.mark.parametrize("n,pairs", [
+    ((256, 256), 1), ((230, 256), 1), ((384, 256), 1), ((360, 400), 1), ((450, 128), 1), ((100, 400), 1),
+    ((70, 37), 0), ((64, 64), 0), ((150, 150), 0), ((128, 256), 0), ((450, 64), 0), ((300, 128), 0),
+    ((150, 400), 0), ((192, 400), 0), ((256, 400), 0), ((64, 4096), 0), ((300, 300), 0)])
+def test_offlattice_in_the_two_cell_kernel(rules, n, pairs):
+    assert rules.pairs(n[0], n[1], 256) == pairs

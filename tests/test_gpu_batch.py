@@ -177,6 +177,40 @@ def test_run_edge_tubes_match_oracle():
 
 
 @gpu
+@pytest.mark.parametrize("base", [2, 60, 124, 480, 992, 1504, 2016, 3008, 4032, 5056])
+def test_run_seam_tubes_match_oracle(base):
+    """tubes about the lengths at which the Euler solve takes another wavefront
+    (64 k - 4 cells of k a lane), another cell per lane or another form (480 k'
+    of two tubes to a block, 3008 to 5056 of one, past that by segments), from
+    states that vary in every cell, so that every seam carries a slope"""
+    rng = np.random.default_rng(base)
+    nv, dv = 16, 0.625
+    sizes = (base - 1, base, base + 1, base // 2 + 1)
+    announce("run seam tubes", sizes)
+    tubes, fields, ref = [], [], []
+    for nx in sizes:
+        x = np.arange(nx) * (2 * np.pi / nx)
+        f = (1.0 + 0.15 * np.sin(x) + 0.05 * rng.uniform(-1, 1, nx), 0.1 * np.sin(x),
+             1.0 + 0.1 * np.cos(x) + 0.05 * rng.uniform(-1, 1, nx))
+        tau = 0.2 / (nx * dv)
+        o = Oracle(1, (nx,), 1.0 / nx, nv, dv, bc=(1,), tau=tau)
+        o.init_macro(f[0], f[1][None], f[2])
+        o.step(4)
+        tubes.append((nx, 1.0 / nx, nv, dv, tau))
+        fields.append(f)
+        ref.append(o)
+    from paper_1212_0204_amd import Batch
+    b = Batch(tubes)
+    b.set_state_macro(*[np.concatenate(a) for a in zip(*fields)])
+    b.set_launch_config(512, 0)  # every tube whole in one block
+    b.step(4)
+    assert (b.tube_flags() == 0).all()
+    for (nx, *_), U, o in zip(tubes, b.read_moments(), ref):
+        err = moment_errors(U, o.U, 1)
+        assert err.max() < TOL32, (nx, err)
+
+
+@gpu
 def test_full_batch_every_tube_8_steps():
     """the 512-tube batch at full size: every tube against the oracle after 8
     steps (1e-5 per moment); a tube may be left out only when both sides

@@ -197,7 +197,7 @@ void hofks_destroy(hofks_ctx *ctx);
  * Many independent 1D-1V tubes (dim 1, outflow, precision 1, scheme 0; n_vel
  * a multiple of 8), each with its own cells, dx, velocity grid, dt = dx/dv
  * and relaxation time, advanced together: per step an Euler launch (one
- * block per tube, two tubes of at most 2048 cells per block, or one block
+ * block per tube, two tubes of at most 2016 cells per block, or one block
  * per part of a split tube) and a kinetic launch (one block per tube
  * segment) run side by side on two streams, then a per-cell update launch;
  * hofks_step replays a captured graph of consecutive steps.  The same
@@ -243,7 +243,8 @@ hofks_status hofks_autotune(hofks_ctx *ctx, int steps, const char *cache_path,
  * run the Euler solve before the kinetic kernel on the context's stream
  * (0: beside it on the library's second stream).  Until this call or
  * hofks_autotune the configuration follows from the grid.  Results do not
- * depend on it beyond the rounding of the moment sums.  HOFKS_EINVAL for a batch or an unavailable choice. */
+ * depend on it beyond the rounding of the moment sums.  HOFKS_EINVAL for a
+ * batch or an unavailable choice. */
 hofks_status hofks_set_launch_config(hofks_ctx *ctx, int wavefronts, int loads, int euler_before);
 
 /* Set the launch configuration of a batch without timing: cells per kinetic

@@ -93,7 +93,7 @@ __device__ __forceinline__ double block_max_1024(double v, double* red) {
 // then the new cell values, written out of place to the other sub-step
 // buffer.  Every flux and every face is computed once (the global-memory
 // form evaluates five fluxes and two faces per cell).  Same helpers (flux1,
-// wsplit, vl_slope_sel, speed1) as the register and part forms, so all
+// wsplit, half_slope, speed1) as the register and part forms, so all
 // three give the same bits; the result is UE[s % 2].
 constexpr int EUL_TPB = 1024;
 constexpr size_t EUL_LDS = (size_t)((EUL_TPB + 4) * 6 + (EUL_TPB + 1) * 3) * sizeof(double);

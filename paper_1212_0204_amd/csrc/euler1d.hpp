@@ -51,7 +51,7 @@ __device__ __forceinline__ double face2(double wp, double hp, double wm, double 
 
 // A wavefront of the group holds 64 CPT consecutive cells, CPT per lane, of
 // which the first and last two are copies of its neighbours' cells, so it
-// advances LINE_OWN(CPT) = 64 CPT - 4 cells.  A sub-step needs two limited slopes
+// advances line_own(CPT) = 64 CPT - 4 cells.  A sub-step needs two limited slopes
 // per cell and moment; the values of the neighbouring lanes (W of one cell on
 // each side, a half state and a face flux) come by one-lane shifts of the ALU.
 // Then every wavefront leaves its edge cells, the row's end cells and its

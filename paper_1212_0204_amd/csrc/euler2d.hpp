@@ -24,8 +24,8 @@ namespace hofks {
 //
 // Bound by latency on small grids (launch, loads, the chain of a strip) and
 // by the FP64 issue rate from about 512^2 cells.  Measured per sub-step
-// against the form it replaced (16 x 16 LDS tiles, four slopes per face pair,
-// four block barriers): alone 9.2 -> 5.4 us on 70 x 37 cells, 8.8 -> 6.4 on
+// against 16 x 16 LDS tiles (four slopes per face pair, four block barriers),
+// which narrow grids keep: alone 9.2 -> 5.4 us on 70 x 37 cells, 8.8 -> 6.4 on
 // 256^2, 25.8 -> 12.3 on 512^2.
 // The flux divergence of the H inner rows of a strip: row(q, U) gives the
 // moments of strip row q (0 .. H + 3, the lane's cell) and done(k, div) takes

@@ -469,7 +469,11 @@ int kin_unroll_euler(const Plan& P, int ng, int unr) {
 }
 
 // Below this lambda the pieces carry nothing of U^{n+1} that a result shows,
-// so the order of sums that are then rounded to FP32 is free.
+// so the order of sums that are then rounded to FP32 is free.  Above it a last
+// bit can flip a rounding to FP32 and move a result by 1e-8, so the forms that
+// round otherwise (the one-block 1D solve, another number of wavefronts) are
+// not taken by rule, though they would be as much faster there: a bound on the
+// results, not a line of speed.
 constexpr double LAM_FREE = 1e-5;
 
 // Wavefronts of an untuned 2D FP32 step while the order of its sums is free
@@ -970,8 +974,8 @@ hofks_status launch_closure_step(hofks_ctx* c, StepArgs<T>& a, float* snap_x, fl
 // 8 -> 18 in 20 steps, a third of all sub-steps ran there when counts were read
 // back 16 steps behind).  The wait keeps at most PEEK_LAG steps queued,
 // more than the host takes to queue one; it polls memory and looks at the
-// stream now and then, so that it ends if the device fails.  On 1D grids
-// the tail is the faster form.
+// stream now and then, so that it ends if the device fails.  1D grids follow
+// nothing: they run in one block, or the tail takes what the spare leaves.
 constexpr int LONG_CALL = 16, PEEK_LAG = 2;
 
 double ring_value(const hofks_ctx* c, unsigned t) {  // < 0: not written

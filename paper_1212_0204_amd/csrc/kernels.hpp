@@ -309,9 +309,9 @@ __device__ __forceinline__ bool lf_speeds(const double* U, double gam, double* s
 }
 
 // The same in 2D from U and 1/rho (rcp_nr), for the wavefront strips.  Each
-// rounding is written out where the compiler placed it when the fluxes and
-// faces went through LDS tiles, which the strips replaced, so results kept
-// their bits: quotients by rho and 2 rho are the reciprocal's product
+// rounding is written out where the compiler places it when the fluxes and
+// faces go through LDS tiles (`k_euler_sub_tile`), so that both give the same
+// bits: quotients by rho and 2 rho are the reciprocal's product
 // corrected by its remainder, which rounds as the division does, and the root
 // is corrected likewise.
 __device__ __forceinline__ void split_flux2(const double* U, double irho, int a, double alpha,

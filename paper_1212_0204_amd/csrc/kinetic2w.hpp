@@ -16,15 +16,17 @@
 // outflow boundary; those lanes load the two pieces separately.
 #pragma once
 #include "kernels.hpp"
+#include "rules.hpp"
 
 namespace hofks {
 
 typedef double w2v __attribute__((ext_vector_type(2)));  // a lane's two pieces
 
 // OFFL: a free time step; the shift of a velocity node in this step replaces
-// its lattice shift (formed once per block, read from LDS as scalars).  256^2 x 32^2 at kinetic CFL 1: the
-// launch 0.216 ms (5.0 TB/s) against 0.244 with one cell per lane, the step
-// 0.262 -> 0.236 ms.
+// its lattice shift (formed once per block, read from LDS as scalars).  256^2 x
+// 32^2 at kinetic CFL 1: the launch 0.216 ms (5.0 TB/s) against 0.244 with one
+// cell per lane, the step 0.262 -> 0.236 ms; see `offlattice_pairs` for where
+// the general kernel is the faster one.
 // Most nodes per axis then: with 76 the four wavefronts' records and the shifts
 // pass 64 KiB.
 constexpr int W2_OFFL_NV = 72;

@@ -76,19 +76,24 @@ inline int fp32_wavefronts(int nx, int nv, long nb, int ncu) {
 }
 
 // Whether an off-lattice 2D FP64 step runs in the two-cell kinetic kernel (128
-// cells of a row to a block) instead of the general one (64): where a launch is
-// more than one block per compute unit and has half as many per unit, to 8%, as
-// the general one.  A lane's second cell doubles its chain, which shows while a
-// unit holds one block, and is wasted on ragged rows.  General against two-cell
-// kernel, us per step, blocks per unit rounded up: 256^2 x 32^2 (4, 2) 273, 242;
-// 384 x 256 x 32^2 (6, 3) 396, 375; 360 x 400 x 32^2 (10, 5) 614, 563; on the
-// other side 150^2 x 16^2 (2, 2) 57, 78; 64^2 x 64^2 (1, 1) 313, 558; 450 x 64 x
-// 32^2 (2, 1) 148, 187; 150 x 400 x 32^2 (5, 4) 339, 432; 300 x 128 x 32^2 (3, 2)
-// 196, 217; 256 x 400 x 32^2 (7, 4) 430, 467.
+// cells of a row to a block) instead of the general one (64), from the blocks
+// per compute unit of either, rounded up.  A lane's second cell doubles its
+// chain, which shows while a unit holds one block, and is wasted on ragged
+// rows; three two-cell blocks run on a unit at a time, so three are one round
+// where five general ones are more, and a fourth starts another.  General
+// against two-cell kernel, us per step with (general, two-cell) blocks per unit:
+// 256^2 x 32^2 (4, 2) 273, 242; 370 x 198 x 32^2 (5, 3) 382, 355; 347 x 222 x 32^2
+// (6, 3) 455, 374; 332 x 371 x 32^2 (9, 5) 633, 583; 360 x 400 x 32^2 (10, 5) 614,
+// 563; on the other side 64^2 x 64^2 (1, 1) 313, 558; 450 x 64 x 32^2 (2, 1) 148,
+// 187; 150^2 x 16^2 (2, 2) 57, 78; 300 x 128 x 32^2 (3, 2) 196, 217; 295 x 197 x 32^2
+// (4, 3) 313, 354; 256 x 400 x 32^2 (7, 4) 430, 467; 296 x 393 x 24^2 (8, 5) 291,
+// 322; and 131 x 375 x 16^2 (5, 3) 106, 127, where a quarter of the lanes is
+// idle.
 inline bool offlattice_pairs(int nx, int ny, int ncu) {
-  const long two = ((long)((nx + W2_CELLS - 1) / W2_CELLS) * ny + ncu - 1) / ncu;
-  const long one = ((long)((nx + 63) / 64) * ny + ncu - 1) / ncu;
-  return two > 1 && 20 * one >= 37 * two;
+  const long b2 = (long)((nx + W2_CELLS - 1) / W2_CELLS) * ny, b1 = (long)((nx + 63) / 64) * ny;
+  const long two = (b2 + ncu - 1) / ncu, one = (b1 + ncu - 1) / ncu;
+  if (two == 1 || 5 * b1 < 8 * b2) return false;
+  return two == 3 ? one >= 5 : 5 * one >= 9 * two;
 }
 
 }  // namespace hofks

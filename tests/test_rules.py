@@ -62,7 +62,8 @@ def test_rows_per_strip(rules, n, fp64, fp32):
 
 @pytest.mark.parametrize("n,pairs", [
     ((256, 256), 1), ((230, 256), 1), ((384, 256), 1), ((360, 400), 1), ((450, 128), 1), ((100, 400), 1),
+    ((370, 198), 1), ((323, 194), 1), ((273, 212), 1), ((332, 371), 1),
     ((70, 37), 0), ((64, 64), 0), ((150, 150), 0), ((128, 256), 0), ((450, 64), 0), ((300, 128), 0),
-    ((150, 400), 0), ((192, 400), 0), ((256, 400), 0), ((64, 4096), 0), ((300, 300), 0)])
+    ((150, 400), 0), ((192, 400), 0), ((256, 400), 0), ((131, 375), 0), ((295, 197), 0), ((296, 393), 0), ((64, 4096), 0), ((300, 300), 0)])
 def test_offlattice_in_the_two_cell_kernel(rules, n, pairs):
     assert rules.pairs(n[0], n[1], 256) == pairs

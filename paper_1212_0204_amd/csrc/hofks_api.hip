@@ -781,7 +781,7 @@ void launch_euler(hofks_ctx* c, const StepArgs<T>& a, hipStream_t st) {
     const int ntx = (P.G.n[0] + ET - 1) / ET, nty = (P.G.n[1] + ET - 1) / ET;
     for (int i = 0; tiles && i < K; ++i)
       hipLaunchKernelGGL((k_euler_sub_tile<T>), dim3(ntx * nty), dim3(256), 0, st, a, P.G, i, ntx);
-    const int H = strip_rows(P.G.n[0], P.G.n[1], sizeof(T) == 4, P.ncu);
+    const int H = strip_rows(P.G.n[0], P.G.n[1], P.G.nv1, sizeof(T) == 4, P.ncu);
     const int nsx = (P.G.n[0] + STRIP_W - 1) / STRIP_W;
     const unsigned nb = (unsigned)strip_blocks(P.G.n[0], P.G.n[1], H);
 #define KE(HH, U)                                                                              \

@@ -24,15 +24,19 @@ inline long strip_blocks(int nx, int ny, int rows) {
 //   3.25 where more than a quarter of the lanes are idle, since blocks that end
 //   soon keep fewer kinetic blocks out (256 x 512 x 32^2 543, 608 with three,
 //   638 with five; 320 x 343 x 24^2 330, 365; 72 x 1527 x 32^2 615, 686; but 400^2
-//   x 32^2, 2.7, 824, 770); then the fewest rows that give each unit at most one
-//   block (364 x 467 x 32^2 776 with four, 791 with five), and five;
+//   x 32^2, 2.7, 824, 770), except with 32 nodes and more in more than five
+//   kinetic blocks per unit (398 x 332 x 32^2 699, 669; 396 x 336 x 32^2 701, 689;
+//   with 24^2 and fewer one row stays ahead); then the fewest rows that give
+//   each unit at most one block (364 x 467 x 32^2 776 with four, 791 with five),
+//   and five;
 // - beside FP32 pieces three rows where those do (256 x 512 x 16^2 166, 180 with
 //   one), else two up to two blocks per unit (128 x 1024 x 32^2 428, 462 with
 //   five; 364 x 467 x 32^2 520, 598), and five.
-inline int strip_rows(int nx, int ny, bool fp32, int ncu) {
+inline int strip_rows(int nx, int ny, int nv, bool fp32, int ncu) {
   const long b1 = strip_blocks(nx, ny, 1);
   const bool idle = 4L * nx < 3L * STRIP_W * ((nx + STRIP_W - 1) / STRIP_W);
-  if (4 * b1 <= (fp32 ? 8L : idle ? 13L : 10L) * ncu) return 1;
+  const bool kinetic = nv >= 32 && (long)((nx + W2_CELLS - 1) / W2_CELLS) * ny > 5L * ncu;
+  if (4 * b1 <= (fp32 ? 8L : idle ? 13L : kinetic ? 8L : 10L) * ncu) return 1;
   if (strip_blocks(nx, ny, 3) <= ncu) return 3;
   if (fp32) return strip_blocks(nx, ny, 2) <= 2L * ncu ? 2 : 5;
   return strip_blocks(nx, ny, 4) <= ncu ? 4 : 5;

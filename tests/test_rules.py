@@ -16,7 +16,9 @@ def rules(tmp_path_factory):
     (d / "r.cpp").write_text('''#include "rules.hpp"
 extern "C" int tiles(int nx, int ny, int ncu) { return hofks::euler_tiles(nx, ny, ncu); }
 extern "C" int pairs(int nx, int ny, int ncu) { return hofks::offlattice_pairs(nx, ny, ncu); }
-extern "C" int rows(int nx, int ny, int fp32, int ncu) { return hofks::strip_rows(nx, ny, fp32, ncu); }
+extern "C" int rows(int nx, int ny, int nv, int fp32, int ncu) {
+  return hofks::strip_rows(nx, ny, nv, fp32, ncu);
+}
 extern "C" int wavefronts(int nx, int ny, int nv, int ncu) {
   return hofks::fp32_wavefronts(nx, nv, (long)((nx + 63) / 64) * ny, ncu);
 }
@@ -57,7 +59,14 @@ def test_fp32_wavefronts(rules, n, nv, w):
     ((400, 400), 3, 3), ((364, 467), 4, 2), ((450, 450), 4, 2),
     ((512, 512), 5, 5), ((1000, 1000), 5, 5)])
 def test_rows_per_strip(rules, n, fp64, fp32):
-    assert (rules.rows(n[0], n[1], 0, 256), rules.rows(n[0], n[1], 1, 256)) == (fp64, fp32)
+    assert (rules.rows(n[0], n[1], 24, 0, 256), rules.rows(n[0], n[1], 24, 1, 256)) == (fp64, fp32)
+
+
+@pytest.mark.parametrize("n,nv,rows", [
+    ((398, 332), 32, 3), ((396, 336), 32, 3), ((398, 332), 24, 1), ((385, 298), 32, 1),
+    ((382, 336), 32, 1), ((72, 1527), 32, 1), ((300, 250), 32, 1)])
+def test_rows_per_strip_beside_long_kinetic_launches(rules, n, nv, rows):
+    assert rules.rows(n[0], n[1], nv, 0, 256) == rows
 
 
 @pytest.mark.parametrize("n,pairs", [
